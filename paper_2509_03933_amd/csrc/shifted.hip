@@ -89,12 +89,31 @@ __device__ __forceinline__ void build_rows(const Coef &coef, int64_t n, int M, i
     T2 *AB = reinterpret_cast<T2 *>(base + L.ab);
     T2 *CM = reinterpret_cast<T2 *>(base + L.cm);
     const int R = P * M;
-    for (int r = threadIdx.x; r < R; r += blockDim.x) {
-        const bool in = r < n;
-        const int p = r / M, j = r - p * M;
-        const int q = p * (M + 1) + j;
-        AB[q] = T2{in && r > 0 ? A[r] : T(0), in ? B[r] : T(1)};
-        CM[q] = T2{in && r < n - 1 ? C[r] : T(0), in ? T(1) : T(0)};
+    // K rows per thread at a time, their loads in flight together (see
+    // dev::rows_commit)
+    constexpr int K = 4;
+    const int nth = (int)blockDim.x;
+    for (int q0 = (int)threadIdx.x; q0 < R; q0 += K * nth) {
+        T a[K], b[K], c[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int64_t r = q0 + (int64_t)k * nth;
+            const int64_t rc = r < n ? r : n - 1;
+            a[k] = A[rc];
+            b[k] = B[rc];
+            c[k] = C[rc];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int r = q0 + k * nth;
+            if (r < R) {
+                const bool in = r < n;
+                const int p = r / M, j = r - p * M;
+                const int q = p * (M + 1) + j;
+                AB[q] = T2{in && r > 0 ? a[k] : T(0), in ? b[k] : T(1)};
+                CM[q] = T2{in && r < n - 1 ? c[k] : T(0), in ? T(1) : T(0)};
+            }
+        }
     }
     __syncthreads();
 }
