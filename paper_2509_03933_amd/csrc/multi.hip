@@ -283,7 +283,7 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
         sh = ((const T *)coef.shift)[sys.valid ? sys.id : 0];
         if (!sys.valid) sh = T(0);
     }
-    dev::rows_commit<T, CR, T>(CO, coef, map.n, R, rr);
+    dev::rows_commit<T, CR, T, 4>(CO, coef, map.n, R, rr);
 #pragma unroll
     for (int j = 0; j < M; ++j)
         if (j >= rows_here) {

@@ -396,7 +396,7 @@ __device__ __forceinline__ void rows_prefetch(const Coef &coef, int64_t n, RowRe
     }
 }
 
-template <typename T, int CR, typename LT = double>
+template <typename T, int CR, typename LT = double, int K = 1>
 __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n, int R,
                                             const RowRegs<CR> &rr) {
     const int nth = (int)blockDim.x;
@@ -413,9 +413,9 @@ __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n,
     // rows beyond CR per thread (blocks with few lanes: small batches), K at a
     // time so that their loads are in flight together: one complex line of 500
     // rows has 32 lanes and 14 such rows each, whose loads one row at a time
-    // were 14 trips to memory in series (launch 22.6 us, now 9.1; 8 at a time
-    // cost the rolling kernel 40 registers more)
-    constexpr int K = 4;
+    // were 14 trips to memory in series (launch 22.6 us, at K = 4 9.1).  The
+    // one-tile-per-block kernels take K = 4; the walking ones keep 1 (the
+    // refinement walk on 14,756 lines of 882 rows: 639 us, at K = 4 711).
     const T *A = (const T *)coef.a, *B = (const T *)coef.b, *C = (const T *)coef.c;
     for (int q = (int)threadIdx.x + CR * nth; q < R; q += K * nth) {
         double a[K], b[K], c[K];
