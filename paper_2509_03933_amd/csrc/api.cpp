@@ -230,6 +230,48 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileShape *o
     return false;
 }
 
+// Batches too small to give every CU a tile or two of the walking kernels
+// (shared operator; strided rows also with a shift or per-row coefficients):
+// the generic kernel with small blocks.  The walking kernels' long unrolled
+// bodies and per-block tables pay over many tiles; on a few, each block runs
+// its code once, cold, and most CUs have none.  16 rows per lane for strided
+// rows (the partition length of the kernels it stands in for, so the
+// interface system and its rounding stay the same), 8 for contiguous ones;
+// blocks of 128 lanes below 2^19 unknowns, 256 (contiguous 512) above.  The
+// block has its lanes whatever the system count: those past the last system
+// load operator rows too.  Walking against generic kernel, us per call in a
+// captured stream, FP64, lines of n rows x systems: shared z-lines 128 x 64
+// 9.7 / 5.1, 1000 x 64 23.1 / 8.7, 1000 x 1024 22.7 / 11.1, 1000 x 2500 28.5 /
+// 18.7, 1000 x 4096 26.1 / 26.6; shifted z-lines 250 x 256 8.5 / 5.7, 1000 x
+// 1024 20.7 / 11.2, 1000 x 2500 27.8 / 19.1, 1000 x 4096 25.4 / 26.9; shared
+// x-lines 250 x 256 18.2 / 8.3, 1000 x 1024 21.1 / 13.7, 777 x 2500 28.9 / 29.0;
+// per-row z-lines 250 x 256 15.6 / 6.1, 1000 x 1024 34.7 / 14.6, 512 x 4096
+// 17.1 / 19.0.  Hence the lines at 3 x 2^20 unknowns, and at 3 x 2^19 for
+// contiguous rows and per-row coefficients.  FP32 per-row lines of up to 128
+// rows stay with the walking kernel (4.5 against 5.1 us).
+static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, TileShape *out) {
+    if (n > 16384 || (like_d && dtype == TDMA_F32 && n <= 128)) return false;
+    const int64_t total = n * nsys;
+    if (total >= (int64_t)3 << (contig || like_d ? 19 : 20)) return false;
+    for (int M : {contig ? 8 : 16, 16}) {
+        const int64_t P = (n + M - 1) / M;
+        const int maxt = fused_max_threads(dtype, M);
+        if (P > maxt) continue;
+        const int64_t lanes = total < ((int64_t)1 << 19) ? 128 : (contig ? 512 : 256);
+        TileShape sh;
+        sh.kernel = 0;
+        sh.M = M;
+        sh.P = (int)P;
+        sh.contig = contig;
+        sh.S_log2 = 4;
+        while (sh.S_log2 > 0 && P << sh.S_log2 > lanes) --sh.S_log2;
+        if (!fused_supported(dtype, sh) || (contig && fused_lds_bytes(dtype, sh) > 96 * 1024)) continue;
+        *out = sh;
+        return true;
+    }
+    return false;
+}
+
 // Shared-operator kernel, streaming form: P a power of two <= 64 (one
 // system's interface rows fit one wavefront), M rows per lane from
 // {16, 32, 8, 12, 24}, the one that pads the system least (P*M - n; 12 and
@@ -676,7 +718,10 @@ int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int
     } else if (!(lookup_tuned(ctx->dev, L, C, dtype, &sh) && sh.contig == contig &&
                  shape_fits(dtype, L, shared_op, sh, shifted_op, perrow_op))) {
         TileShape ssh;
-        if (shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
+        if ((shared_op || (!contig && (shifted_op || perrow_op))) &&
+            small_shape(dtype, L->n, nsys, contig, perrow_op, &ssh))
+            sh = ssh;
+        else if (shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
             shift_layout_ok(make_map(L), ssh))
             sh = ssh;
         else if (perrow_op && !contig && default_perrow_shape(dtype, L->n, nsys, &ssh) &&
