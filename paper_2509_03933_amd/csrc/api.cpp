@@ -192,20 +192,55 @@ static int ilog2_floor(int64_t v) {
     return r;
 }
 
+// Contiguous per-row lines: systems per block (up to 192 lanes) such that the
+// fewest lanes of its wavefronts idle, the smaller block on ties (one
+// wavefront where that loses nothing: its barriers cost nothing).
+static int contig_perrow_s_log2(int64_t P) {
+    int best = 0;
+    double best_use = 0.0;
+    for (int s = 0; s <= 5; ++s) {
+        const int64_t lanes = P << s;
+        if (lanes > 192 && s > 0) break;
+        const double use = (double)lanes / (double)((lanes + 63) / 64 * 64);
+        if (use > best_use + 1e-9) {
+            best = s;
+            best_use = use;
+        }
+    }
+    return best;
+}
+
 // Built-in tile rule for uniform layouts (the autotune cache overrides it).
 // Strided systems: S consecutive systems per tile so that each row load is a
 // full 128-byte line (S = 16 in FP64, 32 in FP32); P partitions of M rows so
 // that P*M covers n.  Contiguous rows: the tile is staged through LDS.
-// Small problems (fewer than 2^20 unknowns) are latency-bound: short
-// partitions (M = 4 first) and one system per tile, so the solve spreads
-// over as many CUs as it can and each lane's serial chain is short.
-bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileShape *out) {
+// Small problems (fewer than 2^20 unknowns; contiguous per-row FP64 lines
+// 2^19) are latency-bound: short partitions (M = 4 first) and one system per
+// tile, so the solve spreads over as many CUs as it can and each lane's
+// serial chain is short.
+// Contiguous per-row FP64 lines beyond that: 8 rows per lane up to 2,048
+// rows.  A lane holds all four inputs of its rows, so 8 rows take half the
+// registers of 16 and twice the blocks run per CU, one's loads beside the
+// other's arithmetic: 120,000 x 720 rows 785 -> 695 us (M = 16, S = 4 against
+// M = 8, S = 2), 120,000 x 250 255 -> 228, 16,384 x 1000 161 -> 135, 40,000 x
+// 1500 552 -> 511; 5,504 x 3000 168 at 16 rows, 209 at 8.  In FP32, 16 rows
+// take those registers already and 8 measured slower (436 against 515 us).
+// Systems per block: contig_perrow_s_log2 (41,856 x 400: S = 1, 50 lanes, 136
+// us, S = 2 149; 27,904 x 600: S = 2, 150 lanes, 157, S = 1 176).
+// Contiguous lines of a shared operator past the streaming kernel's lengths:
+// 8 rows per lane in FP64 and about 512 lanes (16,384 x 2048 315 -> 256 us,
+// 11,136 x 3000 529 -> 365; FP32, 16 rows, 11,136 x 3000 331 -> 220).
+bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shift,
+                   TileShape *out) {
     const int esz = dtype == TDMA_F64 ? 8 : 4;
-    const bool small = n * nsys < ((int64_t)1 << 20);
+    const bool lines = contig && like_d, long_shared = contig && !like_d && !shift;
+    const bool rows8 = dtype == TDMA_F64 && ((lines && n <= 2048) || long_shared);
+    const bool small = n * nsys < ((int64_t)1 << (lines && rows8 ? 19 : 20));
+    const int Ms_rows8[] = {8, 16, 4};
     const int Ms_f64[] = {16, 8, 4};
     const int Ms_f32[] = {16, 32, 8, 4};
     const int Ms_small[] = {4, 8, 16};
-    const int *Ms = small ? Ms_small : (dtype == TDMA_F64 ? Ms_f64 : Ms_f32);
+    const int *Ms = small ? Ms_small : (rows8 ? Ms_rows8 : (dtype == TDMA_F64 ? Ms_f64 : Ms_f32));
     const int nM = small ? 3 : (dtype == TDMA_F64 ? 3 : 4);
     for (int mi = 0; mi < nM; ++mi) {
         const int M = Ms[mi];
@@ -216,6 +251,8 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileShape *o
         sh.P = (int)P;
         sh.contig = contig;
         int S_log2 = contig ? ilog2_floor(std::max<int64_t>(1, 256 / P)) : ilog2_floor(128 / esz);
+        if (lines) S_log2 = contig_perrow_s_log2(P);
+        if (long_shared) S_log2 = ilog2_floor(std::max<int64_t>(1, std::min<int64_t>(16 / esz, 768 / P)));
         const int maxt = fused_max_threads(dtype, M);
         while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
         // a tile larger than the number of systems only wastes lanes
@@ -280,12 +317,18 @@ static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool li
 // partitions (whose interface exchange is DPP row shifts; y-lines of
 // n = 512: 32 rows x 16 partitions 1.84 ms, 16 x 32 1.97-1.99 ms), then the
 // earlier in that order, for contiguous rows the larger M (fewer
-// partitions).  Strided layouts take
+// partitions), in FP64 only up to 24 (the streaming blocks of 32 rows hold
+// 256 lanes) and only where that takes the partitions below 64 or 32 and not
+// below 8 (300,000 x 96: 12 x 8 partitions 92 us, 24 x 4 101).  Strided layouts take
 // S = 32 systems per tile (measured best on the 256^3 ADI sweep in FP64 and
-// FP32), contiguous rows S = 16 and at least 256 lanes; both as far as the
-// lanes and LDS allow.  Contiguous x-lines of n = 768 (FP64): 24 rows x 32
+// FP32), contiguous rows S = 16 and at least 256 lanes (FP64 at 16 rows and
+// 16 partitions or more: S = 8, where two blocks fit a CU's LDS), at most 32;
+// both as far as the lanes and LDS allow.  Contiguous x-lines of n = 768 (FP64): 24 rows x 32
 // partitions x 16 systems 1.94 ms, 12 x 64 x 8 2.26 ms, 24 x 32 x 8 2.68 ms;
-// n = 384: 24 x 16 x 16 0.248 ms, 12 x 32 x 8 0.279 ms.  A streaming
+// n = 384: 24 x 16 x 16 0.248 ms, 12 x 32 x 8 0.279 ms; 167,680 x 200: 16 x 16 x 8
+// 0.118, 16 x 16 x 16 0.130; 480,000 x 250: 0.393, 0.383, 32 x 8 x 32 0.495; 100,000 x 512: 16 x 32 x 8 0.182, 16 x 32 x 16
+// 0.195, 32 x 16 x 16 0.225; 62,500 x 1000: 16 x 64 x 8 0.246, 32 x 32 x 8 0.287.
+// A streaming
 // block holds its CU's LDS for the whole launch, so the whole 160 KB is
 // available to it.  allow_roll admits the rolling form (kernel 6) below; the
 // streamed copy keeps the two-set shape, whose lane bound its kernel shares.
@@ -303,7 +346,9 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
         sh.M = M;
         sh.P = (int)P;
         sh.contig = contig;
-        int S_log2 = contig ? ilog2_floor(std::max<int64_t>(16, 256 / P)) : 5;
+        int64_t S_want = contig ? std::min<int64_t>(32, std::max<int64_t>(16, 256 / P)) : 32;
+        if (contig && dtype == TDMA_F64 && M == 16 && P >= 16) S_want = 8;
+        int S_log2 = ilog2_floor(S_want);
         const int maxt = shared_max_threads(dtype, M, sh.kernel, contig);
         while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
         while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= nsys) --S_log2;
@@ -311,7 +356,8 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
         while (sh.S_log2 > 0 && shared_lds_bytes(dtype, sh) > 160 * 1024) --sh.S_log2;
         if (!shared_supported(dtype, sh)) continue;
         const int64_t pad = (int64_t)sh.P * sh.M, best_pad = found ? (int64_t)best.P * best.M : 0;
-        const bool tie_wins = contig ? sh.M > best.M : (sh.P <= 16 && best.P > 16);
+        const bool tie_wins = contig ? sh.M > best.M && (dtype == TDMA_F32 || (sh.M < 32 && best.P > 8))
+                                     : (sh.P <= 16 && best.P > 16);
         if (!found || pad < best_pad || (pad == best_pad && tie_wins)) {
             best = sh;
             found = true;
@@ -730,7 +776,8 @@ int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int
         else if (shared_op && default_shared_shape(dtype, L->n, nsys, contig, &sh, true)) {
             if (sh.kernel == 6 && !shared_roll_ok(make_map(L), sh))
                 default_shared_shape(dtype, L->n, nsys, contig, &sh, false);
-        } else if (!default_shape(dtype, L->n, nsys, contig, &sh))
+        } else if (!default_shape(dtype, L->n, nsys, contig, C->mode == TDMA_COEF_LIKE_D,
+                                  C->b_shift != nullptr, &sh))
             return fail(TDMA_EUNSUPPORTED, "n = %lld is too long for the fused path (use "
                         "tdma_solve_partitioned)", (long long)L->n);
     }

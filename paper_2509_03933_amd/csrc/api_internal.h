@@ -71,7 +71,8 @@ int get_ctx(DeviceCtx **out);
 int validate(const tdma_layout *L, const tdma_coeffs *C, int dtype, const void *d, const void *x);
 SysMap make_map(const tdma_layout *L);
 Coef make_coef(const tdma_coeffs *C);
-bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileShape *out);
+bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shift,
+                   TileShape *out);
 // min_block: the smallest block of the per-row tile list (lanes): 256 for a
 // batch solved on its own (two blocks share a CU), the kernel's largest block
 // (0 = that) for a batch that runs beside other work, as in a graph.

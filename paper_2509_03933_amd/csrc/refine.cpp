@@ -161,7 +161,8 @@ static int refined_run(const tdma_layout *layout, const tdma_coeffs *coeffs, con
     if (e != hipSuccess) return hip_fail(e, "refine launch");
     if (c.fallback) {
         TileShape fsh;
-        if (!default_shape(TDMA_F64, layout->n, capacity, layout->row_stride == 1, &fsh))
+        if (!default_shape(TDMA_F64, layout->n, capacity, layout->row_stride == 1,
+                           coeffs->mode == TDMA_COEF_LIKE_D, coeffs->b_shift != nullptr, &fsh))
             return fail(TDMA_EUNSUPPORTED, "no FP64 fallback tile for n = %lld", (long long)layout->n);
         SysMap fm = map;
         fm.nsys = capacity;
