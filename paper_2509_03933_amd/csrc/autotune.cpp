@@ -331,8 +331,6 @@ int tdma_autotune(const tdma_layout *layout, const tdma_coeffs *coeffs, int dtyp
     sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
     const SysMap map = make_map(layout);
     const Coef coef = make_coef(coeffs);
-    const bool shared_factors = coeffs->mode == TDMA_COEF_SHARED && coeffs->b_shift == nullptr;
-    const size_t esz = dtype == TDMA_F64 ? 8 : 4;
     js << "{\"path\":\"partitioned\",\"streams\":" << kTuneStreams << ",\"candidates\":[";
     double best_model = 1e300, best_brute = 1e300;
     int64_t s_model = sizes[0], s_brute = sizes[0];
@@ -347,27 +345,13 @@ int tdma_autotune(const tdma_layout *layout, const tdma_coeffs *coeffs, int dtyp
             const int64_t nb_full = std::max<int64_t>(1, nsys / s);   // batches of exactly s systems
             const int K = (int)std::min<int64_t>(kTuneStreams, nb);
             // K batch workspaces (the layout of one pipeline slot each)
-            const size_t fac = shared_factors ? (size_t)layout->n : (size_t)layout->n * s;
-            const size_t fac_bytes = (fac * esz + 255) & ~(size_t)255;
-            const size_t dh_bytes = ((size_t)layout->n * s * esz + 255) & ~(size_t)255;
-            const size_t red_bytes = ((size_t)6 * P * s * 8 + 255) & ~(size_t)255;
-            const size_t x_bytes = ((size_t)2 * P * s * 8 + 255) & ~(size_t)255;
-            const size_t slot_bytes = dh_bytes + 2 * fac_bytes + red_bytes + 2 * x_bytes;
+            std::vector<StageWs> sl(K);
+            const size_t slot_bytes = stage_ws(dtype, coef, layout->n, s, P, nullptr, &sl[0]);
             void *ws = nullptr;
             rc = ctx->workspace(4, slot_bytes * K, &ws);
             if (rc != TDMA_OK) return rc;
-            struct Slot { void *wd, *wa, *wc; double *red, *X, *scr; };
-            std::vector<Slot> sl(K);
-            for (int i = 0; i < K; ++i) {
-                char *b = (char *)ws + slot_bytes * i;
-                sl[i].wd = b;
-                b += dh_bytes;
-                sl[i].wa = b;
-                sl[i].wc = b + fac_bytes;
-                sl[i].red = (double *)(b + 2 * fac_bytes);
-                sl[i].X = (double *)(b + 2 * fac_bytes + red_bytes);
-                sl[i].scr = (double *)(b + 2 * fac_bytes + red_bytes + x_bytes);
-            }
+            for (int i = 0; i < K; ++i)
+                (void)stage_ws(dtype, coef, layout->n, s, P, (char *)ws + slot_bytes * i, &sl[i]);
             // every repetition takes other batches (full ones, so each stage
             // reads what the previous stage wrote for it): a batch's data is
             // not left in the caches by the previous repetition
@@ -376,13 +360,11 @@ int tdma_autotune(const tdma_layout *layout, const tdma_coeffs *coeffs, int dtyp
             auto stage = [&](int which, int i, int64_t k0, hipStream_t q) -> int {
                 hipError_t e;
                 if (which == 0)
-                    e = launch_stage_a(dtype, map, coef, d, sl[i].wd, sl[i].wa, sl[i].wc, sl[i].red, k0, s,
-                                       P, shared_factors, ctx->d_err, q);
+                    e = launch_stage_a(dtype, map, coef, d, sl[i], k0, s, P, ctx->d_err, q);
                 else if (which == 1)
-                    e = launch_stage_b(sl[i].red, sl[i].X, sl[i].scr, s, P, ctx->d_err, q);
+                    e = launch_stage_b(sl[i], s, P, ctx->d_err, q);
                 else
-                    e = launch_stage_c(dtype, map, x, sl[i].wd, sl[i].wa, sl[i].wc, sl[i].X, k0, s, P,
-                                       shared_factors, q);
+                    e = launch_stage_c(dtype, map, coef, d, x, sl[i], k0, s, P, q);
                 return e == hipSuccess ? TDMA_OK : hip_fail(e, "autotune stage");
             };
             // one stage alone, and K instances of it at once on the pipeline's

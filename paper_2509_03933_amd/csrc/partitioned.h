@@ -4,13 +4,24 @@
 
 namespace tdma {
 
+// Workspace of one batch: the recurrence states Stage A keeps for Stage C
+// (nseg per partition), the reduced rows, the interface solution and the
+// scratch of the sequential Stage B.
+struct StageWs {
+    void *ws_d = nullptr, *ws_a = nullptr, *ws_c = nullptr;
+    double *red = nullptr, *X = nullptr, *scratch = nullptr;
+    int nseg = 0;
+};
+
+// Bytes of the workspace for `batch` systems of n rows in P partitions;
+// with mem, `out` points into it (mem null: the size alone).
+size_t stage_ws(int dtype, const Coef &coef, int64_t n, int64_t batch, int P, void *mem, StageWs *out);
+
 hipError_t launch_stage_a(int dtype, const SysMap &map, const Coef &coef, const void *d,
-                          void *ws_d, void *ws_a, void *ws_c, double *red, int64_t k_begin,
-                          int64_t nb, int P, bool shared_factors, int *err, hipStream_t st);
-hipError_t launch_stage_b(const double *red, double *X, double *scratch, int64_t nb, int P,
-                          int *err, hipStream_t st);
-hipError_t launch_stage_c(int dtype, const SysMap &map, void *x, const void *ws_d,
-                          const void *ws_a, const void *ws_c, const double *X, int64_t k_begin,
-                          int64_t nb, int P, bool shared_factors, hipStream_t st);
+                          const StageWs &w, int64_t k_begin, int64_t nb, int P, int *err,
+                          hipStream_t st);
+hipError_t launch_stage_b(const StageWs &w, int64_t nb, int P, int *err, hipStream_t st);
+hipError_t launch_stage_c(int dtype, const SysMap &map, const Coef &coef, const void *d, void *x,
+                          const StageWs &w, int64_t k_begin, int64_t nb, int P, hipStream_t st);
 
 }  // namespace tdma

@@ -5,25 +5,43 @@
 //   tile.hip.h and the running products that turn the back recurrence of the
 //   row-1 spike into a forward sum.  It writes the partition's two
 //   unit-diagonal interface equations (6 values) to the reduced buffer, and
-//   the row factors d^, a^, c^ that Stage C needs to a workspace (never to x,
-//   so inputs and outputs never alias inside a kernel and loads can run ahead).
-// Stage B (k_stage_b): the 2P-row interface system of every system of the
+//   the recurrence's state (d^, a^, c^) at the first row of every segment of
+//   kSeg interior rows to a workspace.
+// Stage B (k_stage_b_pcr, k_stage_b_seq): the 2P-row interface system of every system of the
 //   batch, FP64; parallel cyclic reduction across P consecutive lanes with
 //   wavefront shuffles (P a power of two <= 64), otherwise one lane per system
 //   eliminating the 2P rows in sequence.
-// Stage C (k_stage_c): one lane per (system, partition) walks the partition
-//   backwards: x_{m-1} and x_0 are interface unknowns and
-//   x_j = d^_j - a^_j x_0 - c^_j x_{j+1}.
+// Stage C (k_stage_c): one lane per (system, partition) takes the segments
+//   from the last to the first: the recurrence runs forward again over the
+//   segment's rows from its kept state (the same operations, so the same d^,
+//   a^, c^), into registers, and then backwards x_{m-1} and x_0 being
+//   interface unknowns, x_j = d^_j - a^_j x_0 - c^_j x_{j+1}.  A segment's rows
+//   are read before any of them is written, and a lane reads only rows that
+//   it alone writes, so x may alias d.
+//
+// HBM-bound.  Reading the rows twice costs less than keeping their factors:
+// per unknown (FP64, per-row coefficients) A reads 32 B, C reads 30 and
+// writes 8, the kept states are 1.5 B written and 1.5 read: 73 B against 88
+// with every row's d^, a^, c^ written by A and read by C (shared operator 25
+// against 32, with a shift 27 against 64), and the workspace is a sixteenth.
+// 131,072 per-row lines of 2048 rows (P = 8): 4.77 -> 3.97 ms (73 B: 4.9 TB/s).
 //
 // Partition p of a system of n rows has m_p = floor(n/P) + (p < n mod P) rows
 // starting at p*floor(n/P) + min(p, n mod P).  Every system's arithmetic is
 // independent of how systems are batched, so results are bit-identical for
 // any batch size, stream count or schedule.
+#include <type_traits>
+
 #include "tile.hip.h"
 #include "partitioned.h"
 
 namespace tdma {
 namespace {
+
+// Interior rows per segment: the state kept by Stage A every kSeg rows (24 B in
+// FP64, each way) against the registers that hold a segment's inputs (8 per
+// row).  131,072 per-row lines of 2048 rows: 4.03 ms at 16, 4.13 at 8.
+constexpr int kSeg = 16;
 
 struct PartRange {
     int64_t start;
@@ -44,71 +62,125 @@ __device__ __forceinline__ size_t red_at(int v, int p, int64_t k, int P, int64_t
     return ((size_t)v * P + p) * nb + k;
 }
 
-template <typename T, bool LIKE_D, bool SHIFT, bool SHARED_FACTORS>
-__global__ void __launch_bounds__(256)
-k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
-          T *__restrict__ ws_a, T *__restrict__ ws_c, double *__restrict__ red, int64_t k_begin,
-          int64_t nb, int P, int *err) {
-    const int64_t kl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int p = blockIdx.y;
-    if (kl >= nb) return;
-    const dev::LaneSys sys = dev::lane_system(map, k_begin + kl);
-    const int64_t n = map.n;
-    const PartRange pr = part_range(n, P, p);
-    const T *__restrict__ A = (const T *)coef.a;
-    const T *__restrict__ B = (const T *)coef.b;
-    const T *__restrict__ C = (const T *)coef.c;
-    const int64_t rs = map.row_stride;
-    T sh = T(0);
-    if constexpr (SHIFT) sh = ((const T *)coef.shift)[sys.id];
-    auto load = [&](int64_t r, T &a, T &b, T &c, T &dd) {
-        const int64_t idx = sys.base + r * rs;
+// One row of the matrix as Stage A and C read it: no a_0, no c_{n-1}, the
+// system's shift on the diagonal.
+template <typename T, bool LIKE_D, bool SHIFT>
+struct RowReader {
+    const T *A, *B, *C, *d;
+    int64_t base, rs, n;
+    T sh;
+    __device__ __forceinline__ void load(int64_t r, T &a, T &b, T &c, T &dd) const {
+        const int64_t idx = base + r * rs;
         dd = d[idx];
         if constexpr (LIKE_D) {
             a = A[idx]; b = B[idx]; c = C[idx];
         } else {
             a = A[r]; b = B[r]; c = C[r];
         }
+    }
+    __device__ __forceinline__ void fix(int64_t r, T &a, T &b, T &c) const {
         if constexpr (SHIFT) b += sh;
         if (r == 0) a = T(0);
         if (r == n - 1) c = T(0);
-    };
-    // factor storage: row r of batch-local system kl at r*nb + kl (coalesced)
-    const bool store_factors = !SHARED_FACTORS || kl == 0;
-    const int64_t fk = SHARED_FACTORS ? 0 : kl;
-    const int64_t fstride = SHARED_FACTORS ? 1 : nb;
-    bool bad = false;
-    T a, b, c, dd;
-    load(pr.start, a, b, c, dd);
-    bad |= dev::bad_pivot(b);
-    T ib = dev::recip(b);
-    const T a0 = a * ib, c0 = c * ib, d0 = dd * ib;
-    load(pr.start + 1, a, b, c, dd);
-    bad |= dev::bad_pivot(b);
-    ib = dev::recip(b);
-    T ah = a * ib, ch = c * ib, dh = dd * ib;
-    T pi = T(1), dt1 = T(0), at1 = T(0);
-    const int m = pr.m;
-#pragma unroll 4
-    for (int j = 1; j < m - 1; ++j) {
-        // row j is final: store it, fold it into the row-1 spike, then advance
-        const int64_t r = pr.start + j;
-        ws_d[r * nb + kl] = dh;
-        if (store_factors) {
-            ws_a[r * fstride + fk] = ah;
-            ws_c[r * fstride + fk] = ch;
-        }
-        dt1 += pi * dh;
-        at1 += pi * ah;
-        pi = -ch * pi;
-        load(r + 1, a, b, c, dd);
-        const T piv = b - a * ch;
-        bad |= dev::bad_pivot(piv);
-        ib = dev::recip(piv);
+    }
+};
+
+template <typename T, bool LIKE_D, bool SHIFT>
+__device__ __forceinline__ RowReader<T, LIKE_D, SHIFT> row_reader(const SysMap &map, const Coef &coef,
+                                                                  const T *d, const dev::LaneSys &sys) {
+    RowReader<T, LIKE_D, SHIFT> rd;
+    rd.A = (const T *)coef.a;
+    rd.B = (const T *)coef.b;
+    rd.C = (const T *)coef.c;
+    rd.d = d;
+    rd.base = sys.base;
+    rd.rs = map.row_stride;
+    rd.n = map.n;
+    rd.sh = T(0);
+    if constexpr (SHIFT) rd.sh = ((const T *)coef.shift)[sys.id];
+    return rd;
+}
+
+// The state of the recurrence at one row, and the step to the next row.
+template <typename T>
+struct RowState {
+    T ah, ch, dh;
+    __device__ __forceinline__ T pivot(T a, T b) const { return b - a * ch; }
+    __device__ __forceinline__ void step(T a, T c, T dd, T ib) {
         const T ra = a * ib;
         dh = (dd - a * dh) * ib;
         ch = c * ib;
         ah = -ra * ah;
+    }
+};
+
+// Kept states: segment g of partition p (state of its row 1 + g*kSeg) of
+// batch-local system k at ((p*nseg + g) * nb + k); with a shared operator the
+// same a^, c^ for every system, kept once ((p*nseg + g)).
+template <typename T, bool LIKE_D, bool SHIFT>
+__global__ void __launch_bounds__(256)
+k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
+          T *__restrict__ ws_a, T *__restrict__ ws_c, double *__restrict__ red, int64_t k_begin,
+          int64_t nb, int P, int nseg, int *err) {
+    constexpr bool SHARED_FACTORS = !LIKE_D && !SHIFT;
+    const int64_t kl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.y;
+    if (kl >= nb) return;
+    const dev::LaneSys sys = dev::lane_system(map, k_begin + kl);
+    const PartRange pr = part_range(map.n, P, p);
+    const auto rd = row_reader<T, LIKE_D, SHIFT>(map, coef, d, sys);
+    const int m = pr.m;
+    bool bad = false;
+    T a, b, c, dd;
+    rd.load(pr.start, a, b, c, dd);
+    rd.fix(pr.start, a, b, c);
+    bad |= dev::bad_pivot(b);
+    T ib = dev::recip(b);
+    const T a0 = a * ib, c0 = c * ib, d0 = dd * ib;
+    rd.load(pr.start + 1, a, b, c, dd);
+    rd.fix(pr.start + 1, a, b, c);
+    bad |= dev::bad_pivot(b);
+    ib = dev::recip(b);
+    RowState<T> st{a * ib, c * ib, dd * ib};
+    T pi = T(1), dt1 = T(0), at1 = T(0);
+    // the current row is final: fold it into the row-1 spike, then advance
+    auto advance = [&](int64_t r, T ra, T rb, T rc, T rdd) {
+        dt1 += pi * st.dh;
+        at1 += pi * st.ah;
+        pi = -st.ch * pi;
+        rd.fix(r, ra, rb, rc);
+        const T piv = st.pivot(ra, rb);
+        bad |= dev::bad_pivot(piv);
+        st.step(ra, rc, rdd, dev::recip(piv));
+    };
+    auto keep = [&](int g) {
+        const int64_t q = (int64_t)p * nseg + g;
+        ws_d[q * nb + kl] = st.dh;
+        if constexpr (SHARED_FACTORS) {
+            if (kl == 0) {
+                ws_a[q] = st.ah;
+                ws_c[q] = st.ch;
+            }
+        } else {
+            ws_a[q * nb + kl] = st.ah;
+            ws_c[q * nb + kl] = st.ch;
+        }
+    };
+    // rows 2 .. m-1, a segment's loads in flight together
+    int j = 1, g = 0;
+    for (; j + kSeg <= m - 1; j += kSeg, ++g) {
+        T va[kSeg], vb[kSeg], vc[kSeg], vd[kSeg];
+#pragma unroll
+        for (int i = 0; i < kSeg; ++i) rd.load(pr.start + j + 1 + i, va[i], vb[i], vc[i], vd[i]);
+        keep(g);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kSeg; ++i) advance(pr.start + j + 1 + i, va[i], vb[i], vc[i], vd[i]);
+    }
+    if (j <= m - 2) keep(g);
+    for (; j < m - 1; ++j) {
+        rd.load(pr.start + j + 1, a, b, c, dd);
+        advance(pr.start + j + 1, a, b, c, dd);
     }
     const T ct1 = -pi;
     const double den = 1.0 - (double)c0 * (double)at1;
@@ -117,9 +189,9 @@ k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
     red[red_at(0, p, kl, P, nb)] = rho * (double)a0;
     red[red_at(1, p, kl, P, nb)] = -rho * (double)c0 * (double)ct1;
     red[red_at(2, p, kl, P, nb)] = rho * ((double)d0 - (double)c0 * (double)dt1);
-    red[red_at(3, p, kl, P, nb)] = (double)ah;
-    red[red_at(4, p, kl, P, nb)] = (double)ch;
-    red[red_at(5, p, kl, P, nb)] = (double)dh;
+    red[red_at(3, p, kl, P, nb)] = (double)st.ah;
+    red[red_at(4, p, kl, P, nb)] = (double)st.ch;
+    red[red_at(5, p, kl, P, nb)] = (double)st.dh;
     if (bad) atomicOr(err, 1);
 }
 
@@ -198,96 +270,153 @@ k_stage_b_seq(const double *red, double *X, double *scratch, int64_t nb, int P, 
     if (bad) atomicOr(err, 1);
 }
 
-template <typename T, bool SHARED_FACTORS>
+// d and x may be the same array: no __restrict__ on either.
+template <typename T, bool LIKE_D, bool SHIFT>
 __global__ void __launch_bounds__(256)
-k_stage_c(SysMap map, T *__restrict__ x, const T *__restrict__ ws_d, const T *__restrict__ ws_a,
-          const T *__restrict__ ws_c, const double *__restrict__ X, int64_t k_begin, int64_t nb,
-          int P) {
+k_stage_c(SysMap map, Coef coef, const T *d, T *x, const T *__restrict__ ws_d,
+          const T *__restrict__ ws_a, const T *__restrict__ ws_c, const double *__restrict__ X,
+          int64_t k_begin, int64_t nb, int P, int nseg) {
+    constexpr bool SHARED_FACTORS = !LIKE_D && !SHIFT;
     const int64_t kl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int p = blockIdx.y;
     if (kl >= nb) return;
     const dev::LaneSys sys = dev::lane_system(map, k_begin + kl);
     const PartRange pr = part_range(map.n, P, p);
-    const int64_t rs = map.row_stride;
+    const auto rd = row_reader<T, LIKE_D, SHIFT>(map, coef, d, sys);
+    const int m = pr.m;
     const T xf = (T)X[(size_t)(2 * p) * nb + kl];
     T xn = (T)X[(size_t)(2 * p + 1) * nb + kl];
-    const int64_t fk = SHARED_FACTORS ? 0 : kl;
-    const int64_t fstride = SHARED_FACTORS ? 1 : nb;
-    x[sys.base + (pr.start + pr.m - 1) * rs] = xn;
-#pragma unroll 4
-    for (int j = pr.m - 2; j >= 1; --j) {
-        const int64_t r = pr.start + j;
-        xn = ws_d[r * nb + kl] - ws_a[r * fstride + fk] * xf - ws_c[r * fstride + fk] * xn;
-        x[sys.base + r * rs] = xn;
+    T *xl = x + sys.base + pr.start * rd.rs;   // the partition's row 0
+    xl[(m - 1) * rd.rs] = xn;
+    // segment g: rows j0 = 1 + g*kSeg .. j0 + len - 1 (all interior); FULL: len = kSeg
+    auto segment = [&](int g, int len, auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        const int j0 = 1 + g * kSeg;
+        T va[kSeg], vb[kSeg], vc[kSeg], vd[kSeg];
+#pragma unroll
+        for (int i = 1; i < kSeg; ++i) {
+            const int j = j0 + (FULL || i < len ? i : len - 1);
+            rd.load(pr.start + j, va[i], vb[i], vc[i], vd[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t q = (int64_t)p * nseg + g;
+        RowState<T> st;
+        st.dh = ws_d[q * nb + kl];
+        st.ah = SHARED_FACTORS ? ws_a[q] : ws_a[q * nb + kl];
+        st.ch = SHARED_FACTORS ? ws_c[q] : ws_c[q * nb + kl];
+        // e_j = d^_j - a^_j x_0 and c^_j of the segment's rows
+        vd[0] = st.dh - st.ah * xf;
+        vc[0] = st.ch;
+#pragma unroll
+        for (int i = 1; i < kSeg; ++i) {
+            rd.fix(pr.start + j0 + i, va[i], vb[i], vc[i]);
+            st.step(va[i], vc[i], vd[i], dev::recip(st.pivot(va[i], vb[i])));
+            vd[i] = st.dh - st.ah * xf;
+            vc[i] = st.ch;
+        }
+#pragma unroll
+        for (int i = kSeg - 1; i >= 0; --i) {
+            if (FULL || i < len) {
+                xn = vd[i] - vc[i] * xn;
+                __builtin_nontemporal_store(xn, xl + (j0 + i) * rd.rs);
+            }
+        }
+    };
+    int g = (m - 2 + kSeg - 1) / kSeg - 1;
+    if (g >= 0 && (m - 2) % kSeg != 0) {
+        segment(g, (m - 2) % kSeg, std::false_type{});
+        --g;
     }
-    x[sys.base + pr.start * rs] = xf;
+    for (; g >= 0; --g) segment(g, kSeg, std::true_type{});
+    xl[0] = xf;
+}
+
+#define TDMA_STAGE_DISPATCH(CALL)                                   \
+    if (like_d && !shift) { CALL(true, false); }                    \
+    else if (like_d) { CALL(true, true); }                          \
+    else if (!shift) { CALL(false, false); }                        \
+    else { CALL(false, true); }
+
+template <typename T>
+hipError_t launch_a_t(const SysMap &map, const Coef &coef, const void *d, const StageWs &w, int64_t k_begin,
+                      int64_t nb, int P, int *err, hipStream_t st) {
+    const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)P);
+    const bool like_d = coef.mode == TDMA_COEF_LIKE_D, shift = coef.shift != nullptr;
+#define TDMA_A(LD, SH)                                                                          \
+    hipLaunchKernelGGL((k_stage_a<T, LD, SH>), grid, dim3(256), 0, st, map, coef, (const T *)d, \
+                       (T *)w.ws_d, (T *)w.ws_a, (T *)w.ws_c, w.red, k_begin, nb, P, w.nseg, err)
+    TDMA_STAGE_DISPATCH(TDMA_A)
+#undef TDMA_A
+    return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_a_t(const SysMap &map, const Coef &coef, const void *d, void *ws_d, void *ws_a,
-                      void *ws_c, double *red, int64_t k_begin, int64_t nb, int P, bool shared_f,
-                      int *err, hipStream_t st) {
+hipError_t launch_c_t(const SysMap &map, const Coef &coef, const void *d, void *x, const StageWs &w,
+                      int64_t k_begin, int64_t nb, int P, hipStream_t st) {
     const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)P);
     const bool like_d = coef.mode == TDMA_COEF_LIKE_D, shift = coef.shift != nullptr;
-#define TDMA_A(LD, SH, SF)                                                                      \
-    if (like_d == LD && shift == SH && shared_f == SF) {                                        \
-        hipLaunchKernelGGL((k_stage_a<T, LD, SH, SF>), grid, dim3(256), 0, st, map, coef,       \
-                           (const T *)d, (T *)ws_d, (T *)ws_a, (T *)ws_c, red, k_begin, nb, P, err); \
-        return hipGetLastError();                                                               \
-    }
-    TDMA_A(true, false, false)
-    TDMA_A(true, true, false)
-    TDMA_A(false, false, false)
-    TDMA_A(false, true, false)
-    TDMA_A(false, false, true)
-#undef TDMA_A
-    return hipErrorInvalidValue;
+#define TDMA_C(LD, SH)                                                                          \
+    hipLaunchKernelGGL((k_stage_c<T, LD, SH>), grid, dim3(256), 0, st, map, coef, (const T *)d, \
+                       (T *)x, (const T *)w.ws_d, (const T *)w.ws_a, (const T *)w.ws_c, w.X,    \
+                       k_begin, nb, P, w.nseg)
+    TDMA_STAGE_DISPATCH(TDMA_C)
+#undef TDMA_C
+    return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_stage_a(int dtype, const SysMap &map, const Coef &coef, const void *d,
-                          void *ws_d, void *ws_a, void *ws_c, double *red, int64_t k_begin,
-                          int64_t nb, int P, bool shared_factors, int *err, hipStream_t st) {
-    if (nb <= 0) return hipSuccess;
-    if (dtype == TDMA_F64)
-        return launch_a_t<double>(map, coef, d, ws_d, ws_a, ws_c, red, k_begin, nb, P,
-                                  shared_factors, err, st);
-    return launch_a_t<float>(map, coef, d, ws_d, ws_a, ws_c, red, k_begin, nb, P, shared_factors,
-                             err, st);
+size_t stage_ws(int dtype, const Coef &coef, int64_t n, int64_t batch, int P, void *mem, StageWs *out) {
+    const size_t esz = dtype == TDMA_F64 ? 8 : 4;
+    const auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const int64_t mmax = n / P + (n % P != 0);
+    const int64_t nseg = mmax > 2 ? (mmax - 2 + kSeg - 1) / kSeg : 0;
+    const bool shared_factors = coef.mode == TDMA_COEF_SHARED && coef.shift == nullptr;
+    const size_t states = (size_t)P * nseg;
+    const size_t d_bytes = al(states * batch * esz);
+    const size_t f_bytes = shared_factors ? al(states * esz) : d_bytes;
+    const size_t red_bytes = al((size_t)6 * P * batch * 8), x_bytes = al((size_t)2 * P * batch * 8);
+    char *b = (char *)mem;
+    out->nseg = (int)nseg;
+    if (b) {
+        out->ws_d = b;
+        out->ws_a = b + d_bytes;
+        out->ws_c = b + d_bytes + f_bytes;
+        out->red = (double *)(b + d_bytes + 2 * f_bytes);
+        out->X = (double *)(b + d_bytes + 2 * f_bytes + red_bytes);
+        out->scratch = (double *)(b + d_bytes + 2 * f_bytes + red_bytes + x_bytes);
+    }
+    return d_bytes + 2 * f_bytes + red_bytes + 2 * x_bytes;
 }
 
-hipError_t launch_stage_b(const double *red, double *X, double *scratch, int64_t nb, int P,
-                          int *err, hipStream_t st) {
+hipError_t launch_stage_a(int dtype, const SysMap &map, const Coef &coef, const void *d,
+                          const StageWs &w, int64_t k_begin, int64_t nb, int P, int *err,
+                          hipStream_t st) {
+    if (nb <= 0) return hipSuccess;
+    if (dtype == TDMA_F64) return launch_a_t<double>(map, coef, d, w, k_begin, nb, P, err, st);
+    return launch_a_t<float>(map, coef, d, w, k_begin, nb, P, err, st);
+}
+
+hipError_t launch_stage_b(const StageWs &w, int64_t nb, int P, int *err, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
     if (P <= 64 && (P & (P - 1)) == 0) {
         int P_log2 = 0;
         while ((1 << P_log2) < P) ++P_log2;
         const int64_t lanes = nb * P;
         hipLaunchKernelGGL(k_stage_b_pcr, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st,
-                           red, X, nb, P, P_log2, err);
+                           w.red, w.X, nb, P, P_log2, err);
     } else {
-        hipLaunchKernelGGL(k_stage_b_seq, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, red,
-                           X, scratch, nb, P, err);
+        hipLaunchKernelGGL(k_stage_b_seq, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, w.red,
+                           w.X, w.scratch, nb, P, err);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_stage_c(int dtype, const SysMap &map, void *x, const void *ws_d,
-                          const void *ws_a, const void *ws_c, const double *X, int64_t k_begin,
-                          int64_t nb, int P, bool shared_factors, hipStream_t st) {
+hipError_t launch_stage_c(int dtype, const SysMap &map, const Coef &coef, const void *d, void *x,
+                          const StageWs &w, int64_t k_begin, int64_t nb, int P, hipStream_t st) {
     if (nb <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)P);
-#define TDMA_C(T, SF)                                                                          \
-    hipLaunchKernelGGL((k_stage_c<T, SF>), grid, dim3(256), 0, st, map, (T *)x, (const T *)ws_d, \
-                       (const T *)ws_a, (const T *)ws_c, X, k_begin, nb, P)
-    if (dtype == TDMA_F64) {
-        if (shared_factors) TDMA_C(double, true); else TDMA_C(double, false);
-    } else {
-        if (shared_factors) TDMA_C(float, true); else TDMA_C(float, false);
-    }
-#undef TDMA_C
-    return hipGetLastError();
+    if (dtype == TDMA_F64) return launch_c_t<double>(map, coef, d, x, w, k_begin, nb, P, st);
+    return launch_c_t<float>(map, coef, d, x, w, k_begin, nb, P, st);
 }
 
 }  // namespace tdma

@@ -7,7 +7,7 @@
 // n-1 and Stage C of batch n-2 are issued; A and C go to the "scalable" stream
 // role, B to the "non-scalable" role, and hipEvents replace the host
 // synchronisations, so no host wait happens inside the loop.  Out-of-range
-// batch indices are skipped.  Workspaces (factors, reduced rows, interface
+// batch indices are skipped.  Workspaces (kept states, reduced rows, interface
 // solutions) are triple-buffered by batch index mod 3.  Schedule 1 gives each
 // batch all three stages on stream (batch mod nstreams).
 #include <algorithm>
@@ -20,11 +20,6 @@
 
 namespace tdma {
 
-struct SlotBufs {
-    void *ws_d, *ws_a, *ws_c;
-    double *red, *X, *scratch;
-};
-
 int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int dtype,
                    const void *d, void *x, int P, int64_t batch, int nstreams, int schedule,
                    hipStream_t caller) {
@@ -33,33 +28,28 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
     const int64_t nsys = map.nsys;
     if (nsys == 0) return TDMA_OK;
     const int64_t n = L->n;
-    const size_t esz = dtype == TDMA_F64 ? 8 : 4;
     batch = std::max<int64_t>(1, std::min(batch, nsys));
     const int64_t nbatches = (nsys + batch - 1) / batch;
-    const bool shared_factors = C->mode == TDMA_COEF_SHARED && C->b_shift == nullptr;
     int nslots = schedule == 0 ? 3 : nstreams;
     nslots = (int)std::max<int64_t>(1, std::min<int64_t>(nslots, nbatches));
 
     // per-slot workspace
-    const size_t fac = shared_factors ? (size_t)n : (size_t)n * batch;
-    const size_t fac_bytes = (fac * esz + 255) & ~(size_t)255;
-    const size_t dh_bytes = ((size_t)n * batch * esz + 255) & ~(size_t)255;
-    const size_t red_bytes = ((size_t)6 * P * batch * 8 + 255) & ~(size_t)255;
-    const size_t x_bytes = ((size_t)2 * P * batch * 8 + 255) & ~(size_t)255;
-    const size_t slot_bytes = dh_bytes + 2 * fac_bytes + red_bytes + 2 * x_bytes;
+    std::vector<StageWs> slots(nslots);
+    const size_t slot_bytes = stage_ws(dtype, coef, n, batch, P, nullptr, &slots[0]);
     void *ws = nullptr;
     int rc = ctx->workspace(1, slot_bytes * nslots, &ws);
     if (rc != TDMA_OK) return rc;
-    std::vector<SlotBufs> slots(nslots);
-    for (int i = 0; i < nslots; ++i) {
-        char *b = (char *)ws + slot_bytes * i;
-        slots[i].ws_d = b;
-        b += dh_bytes;
-        slots[i].ws_a = b;
-        slots[i].ws_c = b + fac_bytes;
-        slots[i].red = (double *)(b + 2 * fac_bytes);
-        slots[i].X = (double *)(b + 2 * fac_bytes + red_bytes);
-        slots[i].scratch = (double *)(b + 2 * fac_bytes + red_bytes + x_bytes);
+    for (int i = 0; i < nslots; ++i)
+        (void)stage_ws(dtype, coef, n, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
+
+    // one batch has nothing to overlap with: its three stages run on the
+    // caller's stream, with no fork and join (four streams and eight event
+    // operations otherwise)
+    if (nbatches == 1) {
+        hipError_t e = launch_stage_a(dtype, map, coef, d, slots[0], 0, nsys, P, ctx->d_err, caller);
+        if (e == hipSuccess) e = launch_stage_b(slots[0], nsys, P, ctx->d_err, caller);
+        if (e == hipSuccess) e = launch_stage_c(dtype, map, coef, d, x, slots[0], 0, nsys, P, caller);
+        return e == hipSuccess ? TDMA_OK : hip_fail(e, "pipeline launch");
     }
 
     hipStream_t *streams = nullptr;
@@ -83,18 +73,13 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
     auto nb_of = [&](int64_t b) { return std::min(batch, nsys - b * batch); };
 
     auto stage_a = [&](int64_t b, hipStream_t s) {
-        const SlotBufs &sb = slots[b % nslots];
-        return launch_stage_a(dtype, map, coef, d, sb.ws_d, sb.ws_a, sb.ws_c, sb.red, b * batch,
-                              nb_of(b), P, shared_factors, ctx->d_err, s);
+        return launch_stage_a(dtype, map, coef, d, slots[b % nslots], b * batch, nb_of(b), P, ctx->d_err, s);
     };
     auto stage_b = [&](int64_t b, hipStream_t s) {
-        const SlotBufs &sb = slots[b % nslots];
-        return launch_stage_b(sb.red, sb.X, sb.scratch, nb_of(b), P, ctx->d_err, s);
+        return launch_stage_b(slots[b % nslots], nb_of(b), P, ctx->d_err, s);
     };
     auto stage_c = [&](int64_t b, hipStream_t s) {
-        const SlotBufs &sb = slots[b % nslots];
-        return launch_stage_c(dtype, map, x, sb.ws_d, sb.ws_a, sb.ws_c, sb.X, b * batch, nb_of(b), P,
-                              shared_factors, s);
+        return launch_stage_c(dtype, map, coef, d, x, slots[b % nslots], b * batch, nb_of(b), P, s);
     };
 
     if (schedule == 0) {
