@@ -251,6 +251,8 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
         sh.P = (int)P;
         sh.contig = contig;
         int S_log2 = contig ? ilog2_floor(std::max<int64_t>(1, 256 / P)) : ilog2_floor(128 / esz);
+        // short strided lines: a wavefront's worth of lanes (n = 4: 1283 -> 557 us)
+        while (!contig && S_log2 < 6 && P << S_log2 < 64) ++S_log2;
         if (lines) S_log2 = contig_perrow_s_log2(P);
         if (long_shared) S_log2 = ilog2_floor(std::max<int64_t>(1, std::min<int64_t>(16 / esz, 768 / P)));
         const int maxt = fused_max_threads(dtype, M);
@@ -427,41 +429,40 @@ static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, TileShape *o
     return false;
 }
 
-// Per-row coefficients on strided layouts: the walking kernel with 128-byte
-// tile rows (16 FP64 systems; 16 FP32 systems, 64 bytes).  32 rows per lane
-// (512 lanes) where n is at least 512, else 16; shapes whose partitions cover
-// n exactly (no padding rows) first.  On the 1024^3 per-row z-lines (FP64):
-// 32 rows per lane 10.2 ms, 16 rows 12.6 ms, 16 rows with 64-byte tile rows
-// 20.4 ms.
+// Per-row coefficients on strided layouts: the walking kernel.  P the fewest
+// partitions (a power of two) of at most 32 rows, the rows spread evenly over
+// them; M the slots that hold ceil(n/P) rows (16, 20, 24, 28 or 32).  S
+// systems so that a tile fills 512 lanes (FP32 1024 from 16 partitions on,
+// 512 there for M above 24 unless n fills it), halved to no less than a
+// 128-byte tile row while the tiles are fewer than two per CU.  Measured on
+// 2^26 unknowns in lines along z, us, against the best of 16 and 32 rows per
+// lane with identity rows past the end and 64- or 128-byte tile rows: FP64 n =
+// 100 490, 16 x 8 x 32 545; 500 558, 730; 512 555, 643; 768 603, 914; 1000 640,
+// 829; 1024 711, 711; 1500 912; FP32 300 297, 457; 768 315, 699; 1024 391, 712.
+// FP32 lines that leave M = 32 partly empty go to the generic kernel (1000
+// rows 400 against 414, 1800 507 against 617), and so do lines of fewer than
+// 28 rows (FP64 n = 20: 524 against 819).
 static bool default_perrow_shape(int dtype, int64_t n, int64_t nsys, TileShape *out) {
-    const int Ms[] = {32, 16};
-    TileShape best;
-    bool found = false, best_full = false;
-    for (int M : Ms) {
-        if (M == 32 && n < 512) continue;
-        int64_t P = 2;
-        while (P * M < n) P <<= 1;
-        if (P > 64) continue;
-        TileShape sh;
-        sh.kernel = 5;
-        sh.M = M;
-        sh.P = (int)P;
-        sh.contig = false;
-        const int64_t maxt = M == 32 ? 512 : 1024;
-        int S_log2 = 4;
-        while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
-        while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= nsys) --S_log2;
-        sh.S_log2 = S_log2;
-        if (!perrow_supported(dtype, sh)) continue;
-        const bool full = P * M == n;
-        if (!found || (full && !best_full)) {
-            best = sh;
-            best_full = full;
-            found = true;
-        }
-    }
-    if (found) *out = best;
-    return found;
+    if (n < 28) return false;   // no 16-row slots that two partitions nearly fill
+    int64_t P = 2;
+    while (P * 32 < n) P <<= 1;
+    if (P > 64) return false;
+    TileShape sh;
+    sh.kernel = 5;
+    sh.M = (int)std::max<int64_t>(16, ((n + P - 1) / P + 3) / 4 * 4);
+    sh.P = (int)P;
+    sh.contig = false;
+    const bool full = P * sh.M == n;
+    if (dtype == TDMA_F32 && sh.M == 32 && !full && P >= 32) return false;
+    const bool wide = dtype == TDMA_F32 && P >= 16 && (P > 16 || sh.M <= 24 || full);
+    const int64_t S_min = 128 / (dtype == TDMA_F64 ? 8 : 4);
+    int64_t S = std::min<int64_t>(128, (wide ? 1024 : 512) / P);
+    while (S > S_min && nsys < S * 512) S >>= 1;
+    while (S > 1 && S / 2 >= nsys) S >>= 1;
+    sh.S_log2 = ilog2_floor(S);
+    if (!perrow_supported(dtype, sh)) return false;
+    *out = sh;
+    return true;
 }
 
 // Ragged layout: systems are bucketed by the power-of-two partition count
@@ -725,7 +726,10 @@ static bool shape_fits(int dtype, const tdma_layout *L, bool shared_op, const Ti
         const SysMap m = make_map(L);
         return shift_layout_ok(m, sh);
     }
-    if (sh.kernel == 5) return perrow_op && perrow_supported(dtype, sh) && perrow_layout_ok(make_map(L), sh);
+    if (sh.kernel == 5) {
+        if (!perrow_op || !perrow_supported(dtype, sh) || !perrow_layout_ok(make_map(L), sh)) return false;
+        return sh.M == 16 || sh.M == 32 || perrow_uneven(L->n, sh);
+    }
     if (sh.kernel == 1 || sh.kernel == 2) return shared_op && shared_supported(dtype, sh);
     if (sh.kernel == 6) return shared_op && shared_supported(dtype, sh) && shared_roll_ok(make_map(L), sh);
     if (sh.kernel != 0 || !fused_supported(dtype, sh)) return false;
@@ -889,7 +893,8 @@ int tdma_solve_batched_tiled(const tdma_layout *layout, const tdma_coeffs *coeff
         return fail(TDMA_EINVAL, "unsupported tile M=%d S=%d P=%d", sh.M, S, sh.P);
     if ((sh.kernel == 3 || sh.kernel == 4 || sh.kernel == 7) && !shift_supported(dtype, sh))
         return fail(TDMA_EINVAL, "unsupported shifted-operator tile M=%d S=%d P=%d", sh.M, S, sh.P);
-    if (sh.kernel == 5 && !perrow_supported(dtype, sh))
+    if (sh.kernel == 5 && (!perrow_supported(dtype, sh) || (sh.M != 16 && sh.M != 32) ||
+                           (sh.M == 32 && sh.threads() > 512)))
         return fail(TDMA_EINVAL, "unsupported per-row tile M=%d S=%d P=%d", sh.M, S, sh.P);
     if ((sh.kernel == 1 || sh.kernel == 2 || sh.kernel == 6) && !shared_supported(dtype, sh))
         return fail(TDMA_EINVAL, "unsupported shared-operator tile M=%d S=%d P=%d", sh.M, S, sh.P);

@@ -100,6 +100,7 @@ hipError_t launch_fused_tiles(int dtype, int M, const SysMap &map, const Coef &c
 // workgroups with 128-byte tile rows (perrow.hip)
 bool perrow_supported(int dtype, const TileShape &shape);
 bool perrow_layout_ok(const SysMap &map, const TileShape &shape);
+bool perrow_uneven(int64_t n, const TileShape &shape);
 size_t perrow_lds_bytes(const TileShape &shape);
 hipError_t launch_perrow(int dtype, const SysMap &map, const Coef &coef, const TileShape &shape,
                          const void *d, void *x, int *err_flag, hipStream_t stream);
