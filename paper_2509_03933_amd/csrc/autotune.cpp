@@ -201,6 +201,7 @@ std::vector<TileShape> fused_candidates(int dtype, const tdma_layout *L, const t
 bool lookup_tuned(int dev, const tdma_layout *L, const tdma_coeffs *C, int dtype, TileShape *out) {
     std::lock_guard<std::mutex> g(g_tune_mutex);
     load_cache_locked();
+    if (g_tuned.empty()) return false;   // nothing tuned: no key to format
     auto it = g_tuned.find(key_of(dev, L, C, dtype, "fused", 0));
     if (it == g_tuned.end() || !it->second.has_shape) return false;
     *out = it->second.shape;
@@ -211,6 +212,7 @@ bool lookup_tuned_batch(int dev, const tdma_layout *L, const tdma_coeffs *C, int
                         int64_t *batch, int *nstreams, int *schedule) {
     std::lock_guard<std::mutex> g(g_tune_mutex);
     load_cache_locked();
+    if (g_tuned.empty()) return false;
     auto it = g_tuned.find(key_of(dev, L, C, dtype, "part", *P));
     if (it == g_tuned.end() || it->second.batch <= 0 || it->second.P < 1) return false;
     *P = it->second.P;
