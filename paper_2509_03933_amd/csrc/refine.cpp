@@ -68,28 +68,23 @@ static bool default_shared_refine_shape(int64_t n, int64_t nsys, bool contig, Ti
 }
 
 // Shared operator with a per-system shift on a strided layout (the FFT-Poisson
-// lines): M = 32 rows per lane (else 16), P a power of two <= 64 with
-// P*M >= n, S = 16 consecutive systems (128-byte FP64 rows) as far as the
-// lanes allow (512 at M = 32, else 1024).
+// lines): M = 32 rows per lane, P a power of two <= 64 with P*M >= n, S = 16
+// consecutive systems (128-byte FP64 rows) as far as 512 lanes allow.
 static bool default_shift_refine_shape(const SysMap &map, TileShape *out) {
-    for (int M : {32, 16}) {
-        int64_t P = 1;
-        while (P * M < map.n) P <<= 1;
-        if (P > 64) continue;
-        TileShape sh;
-        sh.M = M;
-        sh.P = (int)P;
-        sh.contig = false;
-        int S_log2 = 4;
-        const int64_t maxt = M == 32 ? 512 : 1024;
-        while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
-        while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= map.nsys) --S_log2;
-        sh.S_log2 = S_log2;
-        if (!shift_refine_supported(map, sh)) continue;
-        *out = sh;
-        return true;
-    }
-    return false;
+    int64_t P = 1;
+    while (P * 32 < map.n) P <<= 1;
+    if (P > 64) return false;
+    TileShape sh;
+    sh.M = 32;
+    sh.P = (int)P;
+    sh.contig = false;
+    int S_log2 = 4;
+    while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > 512) --S_log2;
+    while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= map.nsys) --S_log2;
+    sh.S_log2 = S_log2;
+    if (!shift_refine_supported(map, sh)) return false;
+    *out = sh;
+    return true;
 }
 
 }  // namespace tdma

@@ -529,8 +529,8 @@ k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, 
 }
 
 // ---------------------------------------------------------------------------
-// Precision form on the shifted operator: FP64 d and x per row, FP32 pivot
-// reciprocals g32 and an FP32 work row; per tile
+// Precision form on the shifted operator: FP64 x and an FP32 work row per
+// row; per tile
 //   x = 0, r = d;  repeat 1 + iters times:
 //     solve A e = r with FP32 sweeps (Stage A / C in FP32, the interface
 //     system in FP64), x += e, r = d - A x (FP64, operator rows from LDS);
@@ -538,12 +538,24 @@ k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, 
 // solve and kept; later solves run only the right-hand-side recurrences of
 // Stage A.  A system's convergence is judged from its last two corrections
 // (refine_ratio) and the systems that miss tol are listed for the FP64
-// fallback.  Registers per row: 2 + 2 (d, x) + 1 + 1 (g32, work).
+// fallback.
+//
+// Bound by latency at two waves per SIMD (the LDS of the operator rows and
+// pivots leaves two workgroups per CU), so what counts is what a wave waits
+// for.  The rows of d are not held: a residual reads them again (from the
+// caches, the tile's are 128 KB) through a window of 16 loads in flight, and
+// the registers of x, free from a tile's end to its first correction, take
+// the next tile's rows of d as the rows of x are stored.  Nothing spills (67
+// registers did with d held) and Stage B fits in its DPP form.  512^3 Poisson
+// lines, two steps: 1416 us with d held; 1337 read again at the residual;
+// 1244 with the DPP Stage B; 1008 with the window and the rolled loads (16 B
+// per unknown: 2.1 TB/s).  16 rows per lane (four waves per SIMD, 30
+// registers spilled, twice the interface rows): 1746.
 
 // Second LDS part of the refinement, after the FP64 layout: FP32 copies of
 // the operator rows (a, b, c, m per row, pitch M+1 per partition), then the
 // lanes' FP32 pivot reciprocals (M rows x S*P lanes, lane-contiguous: the
-// registers they would take are what the FP64 d and x need).
+// registers they would take are what the FP64 x needs).
 __host__ __device__ inline size_t shift_refine_lds(int M, int P, int S, size_t *f32_off,
                                                    size_t *g_off = nullptr) {
     const ShiftLds L = shift_layout(sizeof(double), M, P, S);
@@ -553,11 +565,31 @@ __host__ __device__ inline size_t shift_refine_lds(int M, int P, int S, size_t *
     return al16(g + (size_t)M * S * P * sizeof(float));
 }
 
-template <int M, int PQ>
+// The lane's rows of d in memory: row j at element o + j*rs, rows past the
+// system's end (j >= nrow) standing for zeros and read at its last row.
+template <bool FULL>
+struct LaneRows {
+    const double *d;
+    int64_t rs;
+    int nrow;      // rows inside the system (0..M; FULL: all)
+    int back;      // rows the lane's row 0 lies past the system's last row (or 0)
+    // offset of row 0 of a partition at o, and the step from row j to j + 1
+    __device__ __forceinline__ int64_t begin(int64_t o) const {
+        return opaque(FULL ? o : o - (int64_t)back * rs);
+    }
+    __device__ __forceinline__ int64_t next(int64_t q, int j) const {
+        return opaque(q + (FULL || j + 1 < nrow ? rs : 0));
+    }
+    __device__ __forceinline__ double value(int j, double v) const {
+        return FULL || j < nrow ? v : 0.0;
+    }
+};
+
+template <int M, bool FULL, int PQ>
 __device__ __forceinline__ double shift_refine_tile(const char *base, const ShiftLds &L,
                                                     const float4 *R32, float *G, int S, int s, int p, int P,
-                                                    int P_log2, double sh, const double (&dv)[M],
-                                                    double (&xv)[M], int iters, double tol,
+                                                    int P_log2, double sh, const LaneRows<FULL> &rows,
+                                                    int64_t o, double (&xv)[M], int iters, double tol,
                                                     bool valid, int64_t sys_id, RefineState *state) {
     const int tid = threadIdx.x;
     // operator rows through offsets the compiler cannot see through, renewed
@@ -588,14 +620,24 @@ __device__ __forceinline__ double shift_refine_tile(const char *base, const Shif
     double fa = 0.0, fc = 0.0, la = 0.0, lc = 0.0, rho = 0.0;
     float g0 = 0.0f, c0h = 0.0f;
     float ecur = 0.0f, eprev = 0.0f;   // largest entry of the last two corrections
+    // one solve and its correction; the first holds no x yet
+    auto pass = [&](auto first_pass) {
+        constexpr bool FIRST = decltype(first_pass)::value;
+        if constexpr (FIRST) {
+            // x holds the tile's rows of d (loaded as the previous tile was stored)
 #pragma unroll
-    for (int j = 0; j < M; ++j) xv[j] = 0.0;
-    for (int it = 0; it <= iters; ++it) {
-        if (it == 0) {
-#pragma unroll
-            for (int j = 0; j < M; ++j) e[j] = (float)dv[j];
+            for (int j = 0; j < M; ++j) e[j] = (float)rows.value(j, xv[j]);
         } else {
-            // r = d - A x in FP64; the neighbours' outer rows through the exchange
+            // r = d - A x in FP64, the rows of d read again through a window
+            // of loads in flight; the neighbours' outer rows through the exchange
+            constexpr int W = 16;
+            double dv[W];
+            int64_t q = rows.begin(o);
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                dv[j] = rows.d[q];
+                q = rows.next(q, j);
+            }
             __syncthreads();
             XC[s * pitch + 2 * p] = xv[0];
             XC[s * pitch + 2 * p + 1] = xv[M - 1];
@@ -608,7 +650,12 @@ __device__ __forceinline__ double shift_refine_tile(const char *base, const Shif
                 const double2 ab = AB[j], cm = CM[j];
                 const double xm = j == 0 ? xlo : xv[j > 0 ? j - 1 : 0];
                 const double xp = j == M - 1 ? xhi : xv[j < M - 1 ? j + 1 : M - 1];
-                e[j] = (float)(dv[j] - ab.x * xm - (ab.y + cm.y * sh) * xv[j] - cm.x * xp);
+                const double dj = rows.value(j, dv[j % W]);
+                if (j + W < M) {
+                    dv[j % W] = rows.d[q];
+                    q = rows.next(q, j + W);
+                }
+                e[j] = (float)(dj - ab.x * xm - (ab.y + cm.y * sh) * xv[j] - cm.x * xp);
                 if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -617,7 +664,7 @@ __device__ __forceinline__ double shift_refine_tile(const char *base, const Shif
         const float r0v = e[0];
         float dh, dt1, pi = 1.0f;
         rows_group();
-        if (it == 0) {
+        if constexpr (FIRST) {
             float4 q = R4[0];
             float piv = q.y + q.w * shf;
             bad |= dev::bad_pivot(piv);
@@ -706,10 +753,12 @@ __device__ __forceinline__ double shift_refine_tile(const char *base, const Shif
         ecur = 0.0f;
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            xv[j] += (double)e[j];
+            xv[j] = FIRST ? (double)e[j] : xv[j] + (double)e[j];
             ecur = fmaxf(ecur, fabsf(e[j]));
         }
-    }
+    };
+    pass(std::true_type{});
+    for (int it = 1; it <= iters; ++it) pass(std::false_type{});
     // convergence per system: the maxima over its P partitions (adjacent
     // lanes after the exchange, butterfly shuffles); the lane of partition 0
     // judges, misses go to the fallback list
@@ -796,57 +845,50 @@ k_shift_refine(SysMap map, Coef coef, const double *d, double *x, int S_log2, in
         __syncthreads();
     }
     const int nrow = (int)(n - r0 < 0 ? 0 : (n - r0 > M ? M : n - r0));
-    double dv[M], xv[M];
+    double xv[M];
+    LaneRows<FULL> rows;
+    rows.d = d;
+    rows.rs = rs;
+    rows.nrow = nrow;
+    rows.back = nrow > 0 ? 0 : (int)(r0 - (n - 1));
+    double rel = 0.0;
     int64_t b = sbase(w);
     bool ok = w.k < nsys;
     int32_t id = w.k;
     double sh = SH[ok ? w.k : 0];
-    if constexpr (FULL) {
-        int64_t q = (ok ? b : 0) + (int64_t)r0 * rs;
+    int64_t o = (ok ? b : 0) + (int64_t)r0 * rs;
+    {
+        int64_t q = rows.begin(o);
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            dv[j] = __builtin_nontemporal_load(d + q);
-            q = opaque(q + rs);
+            xv[j] = d[q];
+            q = rows.next(q, j);
         }
-    } else {
-        load_lane<double, M>(d, b, ok, rs, r0, n, dv);
     }
-    double rel = 0.0;
     for (;;) {
-        rel = fmax(rel, shift_refine_tile<M, PQ>(base, L, R32, G, S, s, p, P, P_log2, sh, dv, xv, iters, tol,
-                                             ok, id, state));
+        rel = fmax(rel, shift_refine_tile<M, FULL, PQ>(base, L, R32, G, S, s, p, P, P_log2, sh, rows, o, xv,
+                                                       iters, tol, ok, id, state));
         t += gridDim.x;
         const bool more = t < ntiles;
         w.advance(nsys0, step);
         const int64_t nb = sbase(w);
         const bool nok = more && w.k < nsys;
-        const double nsh = SH[nok ? w.k : 0];
-        // store x row by row, each freed register taking the next tile's row
-        // of d (FULL: every row inside the system; otherwise the rows are
-        // clamped to the system's last row and those past it zeroed)
+        sh = SH[nok ? w.k : 0];
+        // each row of x is stored and its register takes the next tile's row of d
         int64_t xq = b + (int64_t)r0 * rs;
-        if constexpr (FULL) {
-            int64_t nq = (nok ? nb : 0) + (int64_t)r0 * rs;
+        o = (nok ? nb : 0) + (int64_t)r0 * rs;
+        int64_t q = rows.begin(o);
 #pragma unroll
-            for (int j = 0; j < M; ++j) {
-                if (ok) __builtin_nontemporal_store(xv[j], x + xq);
-                xq = opaque(xq + rs);
-                dv[j] = __builtin_nontemporal_load(d + nq);
-                nq = opaque(nq + rs);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < M; ++j) {
-                if (ok && j < nrow) __builtin_nontemporal_store(xv[j], x + xq);
-                xq = opaque(xq + rs);
-            }
-            load_lane<double, M>(d, nb, nok, rs, r0, n, dv);
+        for (int j = 0; j < M; ++j) {
+            if (ok && (FULL || j < nrow)) __builtin_nontemporal_store(xv[j], x + xq);
+            xq = opaque(xq + rs);
+            xv[j] = d[q];
+            q = rows.next(q, j);
         }
         if (!more) break;
         b = nb;
         ok = nok;
         id = w.k;
-        sh = nsh;
     }
     if (tid == 0 || (tid & 63) == 0) fold_max_rel(state, rel);
 }
@@ -924,12 +966,15 @@ hipError_t launch_refine_q(const SysMap &map, const Coef &coef, const TileShape 
     return hipGetLastError();
 }
 
-// The precision form keeps the wavefront-shuffle Stage B: the DPP form's
-// extra registers beside its FP64 d and x rows cost more in spills than the
-// shorter interface solve saves (1024^3 Poisson lines: 12.3 against 11.5 ms).
+// 16 and 32 partitions take the DPP form of Stage B (512^3 Poisson lines 1337
+// -> 1244 us), other counts the wavefront-shuffle form.
 template <int M, bool FULL>
 hipError_t launch_refine_m(const SysMap &map, const Coef &coef, const TileShape &sh, const double *d,
                            double *x, int iters, double tol, RefineState *state, hipStream_t st) {
+    switch (sh.P) {
+        case 16: return launch_refine_q<M, FULL, 2>(map, coef, sh, d, x, iters, tol, state, st);
+        case 32: return launch_refine_q<M, FULL, 4>(map, coef, sh, d, x, iters, tol, state, st);
+    }
     return launch_refine_q<M, FULL, 0>(map, coef, sh, d, x, iters, tol, state, st);
 }
 
@@ -961,12 +1006,12 @@ bool shift_layout_ok(const SysMap &m, const TileShape &sh) {
     return 3 * (ntiles + 1) * S < ((int64_t)1 << 31);
 }
 
-// Precision form: M = 16 or 32 rows per lane, P a power of two <= 64,
-// 1024 lanes (512 at M = 32), uniform strided layouts as the FP64 walk.
+// Precision form: 32 rows per lane, P a power of two <= 64, 512 lanes, uniform
+// strided layouts as the FP64 walk.
 bool shift_refine_supported(const SysMap &m, const TileShape &sh) {
-    if (sh.M != 16 && sh.M != 32) return false;
+    if (sh.M != 32) return false;
     if (sh.P < 1 || sh.P > 64 || (sh.P & (sh.P - 1)) != 0) return false;
-    if (sh.S_log2 < 0 || sh.threads() > (sh.M == 32 ? 512 : 1024)) return false;
+    if (sh.S_log2 < 0 || sh.threads() > 512) return false;
     size_t off = 0;
     if (shift_refine_lds(sh.M, sh.P, 1 << sh.S_log2, &off) > 160 * 1024) return false;
     TileShape k = sh;
@@ -980,11 +1025,8 @@ hipError_t launch_shift_refine(const SysMap &map, const Coef &coef, const TileSh
     if (!shift_refine_supported(map, sh) || coef.mode != TDMA_COEF_SHARED || coef.shift == nullptr)
         return hipErrorInvalidValue;
     const bool full = (int64_t)sh.P * sh.M == map.n;
-    if (sh.M == 32)
-        return full ? launch_refine_m<32, true>(map, coef, sh, d, x, iters, tol, state, st)
-                    : launch_refine_m<32, false>(map, coef, sh, d, x, iters, tol, state, st);
-    return full ? launch_refine_m<16, true>(map, coef, sh, d, x, iters, tol, state, st)
-                : launch_refine_m<16, false>(map, coef, sh, d, x, iters, tol, state, st);
+    return full ? launch_refine_m<32, true>(map, coef, sh, d, x, iters, tol, state, st)
+                : launch_refine_m<32, false>(map, coef, sh, d, x, iters, tol, state, st);
 }
 
 hipError_t launch_shift(int dtype, const SysMap &map, const Coef &coef, const TileShape &sh,
