@@ -469,17 +469,16 @@ static bool default_perrow_shape(int dtype, int64_t n, int64_t nsys, TileShape *
 // they need; one launch per non-empty bucket (contiguous rows, LDS-staged).
 // build_ragged_plan allocates the plan's device tables and uploads them
 // synchronously; the caller owns them (free_ragged_plan).
-// Bucket of a ragged system of len rows: M rows per lane (16 in FP64, up to
-// 8,192 rows; 32 and 16 in FP32 at 6,144 rows), P the power of two that
-// covers len / M.  With the four per-row arrays loaded at once and staged
+// Bucket of a ragged system of len rows: 16 rows per lane, P the power of two
+// that covers len / 16.  With the four per-row arrays loaded at once and staged
 // without bank conflicts, 16 rows per lane measured faster than 8 on the
-// longest systems (6,144 rows: 118 against 143 us for 1,245 systems).
-static void ragged_bucket(int dtype, int64_t len, int *M_out, int *P_out) {
-    const int M = dtype == TDMA_F64 ? 16 : (len <= 6144 ? 32 : 16);
-    const int64_t P = (len + M - 1) / M;
+// longest systems (FP64, 6,144 rows: 118 against 143 us for 1,245 systems), and
+// in FP32 than 32 (10,000 systems of 32 to 8,192 rows 133 against 120 us).
+static void ragged_bucket(int64_t len, int *M_out, int *P_out) {
+    const int64_t P = (len + 15) / 16;
     int64_t Pb = 1;
     while (Pb < P) Pb <<= 1;
-    *M_out = M;
+    *M_out = 16;
     *P_out = (int)std::min<int64_t>(Pb, 1 << 30);
 }
 
@@ -495,7 +494,7 @@ int build_ragged_plan(const tdma_layout *L, int dtype, RaggedPlan *out, int min_
     for (int64_t k = 0; k < nsys; ++k) {
         const int64_t len = L->offsets[k + 1] - L->offsets[k];
         int M, P;
-        ragged_bucket(dtype, len, &M, &P);
+        ragged_bucket(len, &M, &P);
         buckets[{M, P}].push_back((int32_t)k);
     }
     for (auto &kv : buckets)

@@ -101,7 +101,7 @@ bool fused_supported(int dtype, const TileShape &sh) {
 }
 
 bool fused_tiles_supported(int dtype, int M) {
-    return dtype == TDMA_F64 ? M == 16 : (dtype == TDMA_F32 && (M == 16 || M == 32));
+    return (dtype == TDMA_F64 || dtype == TDMA_F32) && M == 16;
 }
 
 hipError_t launch_fused_tiles(int dtype, int M, const SysMap &map, const Coef &coef, const void *d,
@@ -115,11 +115,8 @@ hipError_t launch_fused_tiles(int dtype, int M, const SysMap &map, const Coef &c
     if (dtype == TDMA_F64)
         hipLaunchKernelGGL((k_fused_tiles<double, 16>), grid, block, lds, st, map, coef, (const double *)d,
                            (double *)x, tiles, err);
-    else if (M == 16)
-        hipLaunchKernelGGL((k_fused_tiles<float, 16>), grid, block, lds, st, map, coef, (const float *)d,
-                           (float *)x, tiles, err);
     else
-        hipLaunchKernelGGL((k_fused_tiles<float, 32>), grid, block, lds, st, map, coef, (const float *)d,
+        hipLaunchKernelGGL((k_fused_tiles<float, 16>), grid, block, lds, st, map, coef, (const float *)d,
                            (float *)x, tiles, err);
     return hipGetLastError();
 }

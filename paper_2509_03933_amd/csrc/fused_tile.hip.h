@@ -162,6 +162,8 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
         pdd_interface(lds, S, s, p, P, f, xf, xl, bad);
     else if (P <= 64 && (P & (P - 1)) == 0)
         dev::pcr_interface_wave(lds, S, s, p, P, __builtin_ctz(P), f, xf, xl, bad);
+    else if (P > 64)
+        dev::two_level_interface(lds, S, s, p, P, f, xf, xl, bad);
     else
         dev::pcr_interface(lds, S, s, p, P, f, xf, xl, bad);
     dev::substitute_partition<T, M>(av, cv, dv, xf, xl);
@@ -285,6 +287,8 @@ __device__ __forceinline__ void fused_tile_co(const SysMap &map, const Coef &coe
         pdd_interface(lds, S, s, p, P, f, xf, xl, bad);
     else if (P <= 64 && (P & (P - 1)) == 0)
         dev::pcr_interface_wave(lds, S, s, p, P, __builtin_ctz(P), f, xf, xl, bad);
+    else if (P > 64)
+        dev::two_level_interface(lds, S, s, p, P, f, xf, xl, bad);
     else
         dev::pcr_interface(lds, S, s, p, P, f, xf, xl, bad);
     dev::substitute_partition<T, M>(ah, ch, dv, xf, xl);

@@ -89,8 +89,8 @@ struct RaggedTile {
     int32_t first, count;
     int32_t P_log2, S_log2;
 };
-// per-row coefficients without a shift, contiguous rows; M = 16 (FP64) or
-// 16, 32 (FP32); `threads` lanes per block for every tile of the list
+// per-row coefficients without a shift, contiguous rows; M = 16; `threads`
+// lanes per block for every tile of the list
 bool fused_tiles_supported(int dtype, int M);
 hipError_t launch_fused_tiles(int dtype, int M, const SysMap &map, const Coef &coef, const void *d,
                               void *x, const RaggedTile *tiles, int64_t ntiles, int threads,

@@ -107,10 +107,16 @@ __device__ __forceinline__ LaneSys lane_system(const SysMap &m, int64_t k) {
     return r;
 }
 
+// Slots per system of the two-level interface solve: 64 groups of K rows and
+// one spare slot each, K = ceil(2P / 64).
+__host__ __device__ constexpr int two_level_rows(int P) { return (2 * P + 63) / 64; }
+__host__ __device__ constexpr int two_level_pitch(int P) { return 64 * (two_level_rows(P) + 1); }
+
 // LDS bytes of Stage B for S systems x P partitions: three arrays (a, c, d)
-// of 2P rows per system plus one pad row (both PCR variants fit in this).
+// of 2P rows per system plus one pad row (the PCR variants), or the two-level
+// solve's slots above 64 partitions.
 __host__ __device__ constexpr size_t pcr_lds_bytes(int S, int P) {
-    return (size_t)3 * S * (2 * P + 1) * sizeof(double);
+    return (size_t)3 * S * (P > 64 ? two_level_pitch(P) : 2 * P + 1) * sizeof(double);
 }
 
 // Interface rows of one partition (unit diagonal): first row couples
@@ -357,6 +363,110 @@ __device__ __forceinline__ void pcr_interface_wave(double *lds, int S, int s, in
     __syncthreads();
     x_first = rd[s * pitch + 2 * p];
     x_last = rd[s * pitch + 2 * p + 1];
+}
+
+// Stage B for more than 64 partitions: the system's 2P interface rows are
+// themselves partitioned.  The rows go to LDS; wavefront w takes system w, its
+// lane l the K = ceil(2P / 64) consecutive rows from l*K (identity rows past
+// 2P), which it reduces to two rows by the same modified Thomas sweep as
+// Stage A (unit diagonals; a^, c^, d^ kept in place), the 128 rows of the
+// wavefront are solved by PCR with shuffles as in pcr_interface_wave, and the
+// lane substitutes back.  Against one PCR over all 2P rows in LDS
+// (pcr_interface: log2(2P) steps of 18 accesses per lane and two barriers),
+// three barriers in all.  A group has K + 1 slots, so the lanes of a wavefront
+// read their rows from different banks.  S*P >= 64 S lanes: every system finds
+// its wavefront.  Every thread calls it.  Contiguous per-row FP64 lines, 2^24
+// unknowns: n = 1500 150 -> 141 us, 5000 259 -> 241, 8000 216 -> 207; 40,000
+// FP32 systems of 32 to 8,192 rows 414 -> 364.
+__device__ __forceinline__ void two_level_interface(double *lds, int S, int s, int p, int P, Iface f,
+                                                    double &x_first, double &x_last, bool &bad) {
+    const int K = two_level_rows(P), pitch = two_level_pitch(P);
+    double *ra = lds, *rc = lds + S * pitch, *rd = lds + 2 * S * pitch;
+    const int i0 = 2 * p, i1 = 2 * p + 1;
+    const int q0 = s * pitch + i0 + i0 / K, q1 = s * pitch + i1 + i1 / K;
+    __syncthreads();
+    ra[q0] = f.fa; rc[q0] = f.fc; rd[q0] = f.fd;
+    ra[q1] = f.la; rc[q1] = f.lc; rd[q1] = f.ld;
+    __syncthreads();
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (w < S) {
+        const int R2 = 2 * P;
+        const int r0 = l * K;
+        double *A = ra + w * pitch + l * (K + 1), *C = rc + w * pitch + l * (K + 1),
+               *D = rd + w * pitch + l * (K + 1);
+        auto row = [&](int j, double &a, double &c, double &d) {
+            const bool in = r0 + j < R2;
+            a = in ? A[j] : 0.0;
+            c = in ? C[j] : 0.0;
+            d = in ? D[j] : 0.0;
+        };
+        double a0, c0, d0, ah, ch, dh;
+        row(0, a0, c0, d0);
+        row(1, ah, ch, dh);
+        double pi = 1.0, dt1 = dh, at1 = ah;      // K >= 3: row 1 is interior
+        double a, c, d;
+        row(2, a, c, d);
+        for (int j = 2; j < K; ++j) {
+            double an = 0.0, cn = 0.0, dn = 0.0;
+            if (j + 1 < K) row(j + 1, an, cn, dn);
+            const double piv = 1.0 - a * ch;
+            bad |= bad_pivot(piv);
+            const double g = recip(piv);
+            const double ag = a * g;
+            dh = (d - a * dh) * g;
+            ah = -ag * ah;
+            pi = -ch * pi;
+            ch = c * g;
+            if (j < K - 1) {
+                dt1 += pi * dh;
+                at1 += pi * ah;
+                A[j] = ah;
+                C[j] = ch;
+                D[j] = dh;
+            }
+            a = an; c = cn; d = dn;
+        }
+        const double den = 1.0 - c0 * at1;
+        bad |= bad_pivot(den);
+        const double rho = recip(den);
+        double fa = rho * a0, fc = rho * c0 * pi, fd = rho * (d0 - c0 * dt1);
+        {
+            // distance 1: the first row meets the last row of lane - 1 and its
+            // own last row, the last row its own first and that of lane + 1
+            const bool has_lo = l > 0, has_hi = l < 63;
+            const int lo = has_lo ? l - 1 : l, hi = has_hi ? l + 1 : l;
+            double am = __shfl(ah, lo), cm = __shfl(ch, lo), dm = __shfl(dh, lo);
+            double ap = __shfl(fa, hi), cp = __shfl(fc, hi), dp = __shfl(fd, hi);
+            if (!has_lo) { am = 0.0; cm = 0.0; dm = 0.0; }
+            if (!has_hi) { ap = 0.0; cp = 0.0; dp = 0.0; }
+            const double oa = fa, oc = fc, od = fd;
+            pcr_row(fa, fc, fd, am, cm, dm, ah, ch, dh, bad);
+            pcr_row(ah, ch, dh, oa, oc, od, ap, cp, dp, bad);
+        }
+        for (int dl = 1; dl < 64; dl <<= 1) {
+            const bool has_lo = l >= dl, has_hi = l + dl < 64;
+            const int lo = has_lo ? l - dl : l, hi = has_hi ? l + dl : l;
+            double la0 = __shfl(fa, lo), lc0 = __shfl(fc, lo), ld0 = __shfl(fd, lo);
+            double la1 = __shfl(ah, lo), lc1 = __shfl(ch, lo), ld1 = __shfl(dh, lo);
+            double ua0 = __shfl(fa, hi), uc0 = __shfl(fc, hi), ud0 = __shfl(fd, hi);
+            double ua1 = __shfl(ah, hi), uc1 = __shfl(ch, hi), ud1 = __shfl(dh, hi);
+            if (!has_lo) { la0 = lc0 = ld0 = la1 = lc1 = ld1 = 0.0; }
+            if (!has_hi) { ua0 = uc0 = ud0 = ua1 = uc1 = ud1 = 0.0; }
+            pcr_row(fa, fc, fd, la0, lc0, ld0, ua0, uc0, ud0, bad);
+            pcr_row(ah, ch, dh, la1, lc1, ld1, ua1, uc1, ud1, bad);
+        }
+        // fd, dh are the group's outer unknowns: the rows between
+        double xn = dh;
+        for (int j = K - 2; j >= 1; --j) {
+            xn = D[j] - A[j] * fd - C[j] * xn;
+            D[j] = xn;
+        }
+        D[0] = fd;
+        D[K - 1] = dh;
+    }
+    __syncthreads();
+    x_first = rd[q0];
+    x_last = rd[q1];
 }
 
 template <typename T>
