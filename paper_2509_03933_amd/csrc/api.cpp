@@ -287,11 +287,31 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
 // per-row z-lines 250 x 256 15.6 / 6.1, 1000 x 1024 34.7 / 14.6, 512 x 4096
 // 17.1 / 19.0.  Hence the lines at 3 x 2^20 unknowns, and at 3 x 2^19 for
 // contiguous rows and per-row coefficients.  FP32 per-row lines of up to 128
-// rows stay with the walking kernel (4.5 against 5.1 us).
-static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, TileShape *out) {
+// rows stay with the walking kernel (4.5 against 5.1 us).  FP32 batches of a
+// shared operator keep the shared-operator kernel, whose factors are formed in
+// FP64, with small tiles of short partitions (one tile per block on strided
+// rows): z-lines 250 x 64 11.6 -> 8.0 us, 1000 x 1024 16.9 -> 13.2, x-lines 250 x
+// 64 17.3 -> 8.6, 1000 x 1024 25.1 -> 12.9.
+static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shared_op,
+                        TileShape *out) {
     if (n > 16384 || (like_d && dtype == TDMA_F32 && n <= 128)) return false;
     const int64_t total = n * nsys;
     if (total >= (int64_t)3 << (contig || like_d ? 19 : 20)) return false;
+    if (shared_op && dtype == TDMA_F32) {
+        TileShape sh;
+        sh.kernel = contig ? 2 : 1;
+        sh.M = n <= 256 ? 8 : (n <= 1024 ? 16 : (n <= 1536 ? 24 : 32));
+        if (n > 64 * (int64_t)sh.M) return false;
+        sh.P = 1;
+        while ((int64_t)sh.P * sh.M < n) sh.P <<= 1;
+        sh.contig = contig;
+        const int lanes = total >= ((int64_t)1 << 19) ? 512 : (sh.P > 32 ? 256 : 128);
+        sh.S_log2 = 4;
+        while (sh.S_log2 > 0 && sh.P << sh.S_log2 > lanes) --sh.S_log2;
+        if (!shared_supported(dtype, sh)) return false;
+        *out = sh;
+        return true;
+    }
     for (int M : {contig ? 8 : 16, 16}) {
         const int64_t P = (n + M - 1) / M;
         const int maxt = fused_max_threads(dtype, M);
@@ -768,7 +788,7 @@ int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int
                  shape_fits(dtype, L, shared_op, sh, shifted_op, perrow_op))) {
         TileShape ssh;
         if ((shared_op || (!contig && (shifted_op || perrow_op))) &&
-            small_shape(dtype, L->n, nsys, contig, perrow_op, &ssh))
+            small_shape(dtype, L->n, nsys, contig, perrow_op, shared_op, &ssh))
             sh = ssh;
         else if (shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
             shift_layout_ok(make_map(L), ssh))
