@@ -407,42 +407,53 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
 }
 
 // Shared operator with a per-system shift on a strided layout (the
-// FFT-Poisson lines): M = 32 rows per lane (else 16, 8), P a power of two
-// <= 64 with P*M >= n, and S = 16 consecutive systems per tile in FP64, 32 in
-// FP32 (128-byte tile rows), as far as the lanes allow (512 for FP64 at
-// M = 32, else 1024); the rolling walk (kernel 3).  In FP64 with 32 rows per
-// lane and 16 or 32 partitions covering n, the walk that recomputes its
-// pivots (kernel 7) with S = 32 (256-byte rows).  Measured on the 1024^3
-// Poisson lines in FP64: kernel 7 with 32 x 32 partitions x 32 rows 3.9 ms;
-// kernel 3 with 16 x 32 x 32 4.5 ms, 16 x 64 x 16 6.0 ms, 8 x 32 x 32 7.3 ms;
-// on 1024^2 x 512 lines kernel 7 with 32 x 16 x 32 1.87 ms, kernel 3 with
-// 16 x 16 x 32 2.54 ms.
+// FFT-Poisson lines).  FP64 above 256 rows: the walk that recomputes its pivots
+// (kernel 7), P the fewest partitions (16, 32 or 64) of at most 32 rows, the
+// rows spread evenly over them in M = 20, 24, 28 or 32 slots, and S = 32
+// consecutive systems (256-byte rows; 16 with 64 partitions).  Up to 256 rows:
+// lengths that fill partitions of 32 rows take the rolling walk that keeps
+// its pivots (kernel 3) with S = 32, others the generic kernel (false).  FP32:
+// kernel 3, M = 32 rows per lane (else 16, 8), P a power of two <= 64, S = 32.
+// Measured on 2^27 unknowns in lines along z (FP64, us): n = 1024 kernel 7 509,
+// kernel 3 with 16 x 32 x 32 538, 16 x 64 x 16 675; n = 300 kernel 7 480, kernel 3
+// with identity rows past the end 729, 640 495 and 797, 1000 540 and 629, 2048
+// 665 and 1043; n = 64 kernel 3
+// 453 (S = 16 498, kernel 7 472), 256 458 (538, 494); n = 40 generic 498, kernel
+// 3 with identity rows 1158, 100 464 and 624, 200 488 and 647.
 static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, TileShape *out) {
-    const int Ms[] = {32, 16, 8};
-    for (int M : Ms) {
+    TileShape sh;
+    sh.contig = false;
+    if (dtype == TDMA_F64) {
+        int64_t P = 1;
+        while (P * 32 < n) P <<= 1;
+        if (P > 64) return false;
+        sh.P = (int)P;
+        if (n <= 256) {
+            if (P * 32 != n) return false;
+            sh.kernel = 3;
+            sh.M = 32;
+        } else {
+            sh.kernel = 7;
+            sh.M = (int)(((n + P - 1) / P + 3) / 4 * 4);
+        }
+        sh.S_log2 = P > 32 ? 4 : 5;
+        while (sh.S_log2 > 0 && ((int64_t)1 << (sh.S_log2 - 1)) >= nsys) --sh.S_log2;
+        if (!shift_uneven(n, sh) && !shift_supported(dtype, sh)) return false;
+        *out = sh;
+        return true;
+    }
+    for (int M : {32, 16, 8}) {
         int64_t P = 1;
         while (P * M < n) P <<= 1;
         if (P > 64) continue;
-        TileShape sh;
         sh.kernel = 3;
         sh.M = M;
         sh.P = (int)P;
-        sh.contig = false;
-        const int64_t maxt = dtype == TDMA_F64 && M == 32 ? 512 : 1024;
-        int S_log2 = dtype == TDMA_F64 ? 4 : 5;
-        while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
+        int S_log2 = 5;
+        while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > 1024) --S_log2;
         while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= nsys) --S_log2;
         sh.S_log2 = S_log2;
         if (!shift_supported(dtype, sh)) continue;
-        // FP64, 32 rows per lane, 16 or 32 partitions covering n: the kernel
-        // that recomputes its pivots fits 32 systems (256-byte rows)
-        if (dtype == TDMA_F64 && M == 32 && (P == 16 || P == 32) && P * M == n) {
-            TileShape w = sh;
-            w.kernel = 7;
-            w.S_log2 = 5;
-            while (w.S_log2 > 0 && ((int64_t)1 << (w.S_log2 - 1)) >= nsys) --w.S_log2;
-            if (w.S_log2 > sh.S_log2 && shift_supported(dtype, w)) sh = w;
-        }
         *out = sh;
         return true;
     }

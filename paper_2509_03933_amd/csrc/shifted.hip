@@ -80,8 +80,30 @@ __host__ __device__ inline ShiftLds shift_layout(size_t esz, int M, int P, int S
     return L;
 }
 
-// The tile's operator rows into LDS (once per workgroup), identity rows past n.
-template <typename T>
+// Uneven partitions (n not P*M): n mod P partitions of floor(n/P) + 1 rows,
+// the rest of floor(n/P), in M row slots of which at most kSlack stay empty.
+// Rows 0 .. cnt-2 of a partition fill slots 0 .. cnt-2 and its last row slot
+// M-1; the slots between are passed over: the recurrences keep their state,
+// nothing is stored, and a load there repeats a row.
+constexpr int kSlack = 4;
+
+// The row of slot j of partition p (-1: none) of n rows in P = 2^P_log2
+// partitions of M slots.
+template <bool UNEVEN>
+__device__ __forceinline__ int64_t slot_row(int64_t n, int M, int P_log2, int p, int j) {
+    if constexpr (!UNEVEN) {
+        const int64_t r = (int64_t)p * M + j;
+        return r < n ? r : -1;
+    } else {
+        const int q = (int)n >> P_log2, rem = (int)n & ((1 << P_log2) - 1);
+        const int start = p * q + (p < rem ? p : rem), cnt = q + (p < rem ? 1 : 0);
+        return j < cnt - 1 ? start + j : (j == M - 1 ? start + cnt - 1 : -1);
+    }
+}
+
+// The tile's operator rows into LDS (once per workgroup), identity rows in
+// the slots without one.
+template <typename T, bool UNEVEN = false>
 __device__ __forceinline__ void build_rows(const Coef &coef, int64_t n, int M, int P, char *base,
                                            const ShiftLds &L) {
     using T2 = typename Pair2<T>::type;
@@ -93,12 +115,15 @@ __device__ __forceinline__ void build_rows(const Coef &coef, int64_t n, int M, i
     // dev::rows_commit)
     constexpr int K = 4;
     const int nth = (int)blockDim.x;
+    const int P_log2 = __builtin_ctz(P);
     for (int q0 = (int)threadIdx.x; q0 < R; q0 += K * nth) {
         T a[K], b[K], c[K];
+        int64_t row[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const int64_t r = q0 + (int64_t)k * nth;
-            const int64_t rc = r < n ? r : n - 1;
+            const int r = q0 + k * nth, p = r / M;
+            row[k] = r < R ? slot_row<UNEVEN>(n, M, P_log2, p, r - p * M) : -1;
+            const int64_t rc = row[k] >= 0 ? row[k] : 0;
             a[k] = A[rc];
             b[k] = B[rc];
             c[k] = C[rc];
@@ -107,11 +132,10 @@ __device__ __forceinline__ void build_rows(const Coef &coef, int64_t n, int M, i
         for (int k = 0; k < K; ++k) {
             const int r = q0 + k * nth;
             if (r < R) {
-                const bool in = r < n;
-                const int p = r / M, j = r - p * M;
-                const int q = p * (M + 1) + j;
-                AB[q] = T2{in && r > 0 ? a[k] : T(0), in ? b[k] : T(1)};
-                CM[q] = T2{in && r < n - 1 ? c[k] : T(0), in ? T(1) : T(0)};
+                const bool in = row[k] >= 0;
+                const int q = r + r / M;
+                AB[q] = T2{in && row[k] > 0 ? a[k] : T(0), in ? b[k] : T(1)};
+                CM[q] = T2{in && row[k] < n - 1 ? c[k] : T(0), in ? T(1) : T(0)};
             }
         }
     }
@@ -130,7 +154,7 @@ struct LaneIo {
     int64_t xo;        // row 0 of the lane's partition in x (elements)
     int64_t no;        // row 0 of the lane's partition of the next tile in d (ROLL)
     int64_t rs;        // row stride (elements)
-    int nrow;          // rows of the partition inside the system (0..M)
+    int nrow;          // rows of the partition inside the system (0..M; uneven: its rows)
     bool valid;        // the lane's system exists (else nothing is stored)
 };
 
@@ -275,7 +299,10 @@ __device__ __forceinline__ void shift_solve(const char *base, const ShiftLds &L,
 // tile can be 32 FP64 systems (256-byte rows) wide.  The partitions cover n
 // exactly, so every row is a system row (m_j = 1: the shift is added as is)
 // and a row's operator reads are (a_j, b_j) and c_j, 24 of the 32 bytes.
-template <int M, int FL, int K, int PQ>
+// UNEVEN: the partition has io.nrow rows in its M slots (2^27 unknowns in lines
+// of 640 rows, 20 slots: 0.495 ms, 4.3 TB/s; identity rows past the end in 32
+// rows per lane: 0.797).
+template <int M, int FL, int K, int PQ, bool UNEVEN>
 __device__ __forceinline__ void shift_solve_recomp(const char *base, const ShiftLds &L, int S, int s,
                                                    int p, int P, int P_log2, double sh,
                                                    double (&v)[M], const LaneIo<double> &io,
@@ -284,6 +311,11 @@ __device__ __forceinline__ void shift_solve_recomp(const char *base, const Shift
     using T = double;
     using T2 = double2;
     auto slot = [](int j) { return FL == 1 ? M - 1 - j : j; };
+    // slots that may be passed over, and whether slot j holds a row
+    const int cnt = UNEVEN ? opaque(io.nrow) : M;
+    auto maybe = [](int j) { return UNEVEN && j >= M - 1 - kSlack && j < M - 1; };
+    auto have = [&](int j) { return !maybe(j) || j < cnt - 1; };
+    auto sel = [&](int j, T now, T old) { return maybe(j) ? (have(j) ? now : old) : now; };
     const int q0 = p * (M + 1);
     const T2 *AB0 = reinterpret_cast<const T2 *>(base + L.ab);
     const T2 *CM0 = reinterpret_cast<const T2 *>(base + L.cm);
@@ -319,15 +351,15 @@ __device__ __forceinline__ void shift_solve_recomp(const char *base, const Shift
         ab = AB[j];
         cm = CM[j];
         piv = (ab.y + sh) - ab.x * ch;
-        bad |= dev::bad_pivot(piv);
+        bad |= have(j) && dev::bad_pivot(piv);
         gj = dev::recip(piv);
-        dh = (v[slot(j)] - ab.x * dh) * gj;
-        ah = -(ab.x * gj) * ah;
-        pi = -ch * pi;
-        ch = cm.x * gj;
+        dh = sel(j, (v[slot(j)] - ab.x * dh) * gj, dh);
+        ah = sel(j, -(ab.x * gj) * ah, ah);
+        pi = sel(j, -ch * pi, pi);
+        ch = sel(j, cm.x * gj, ch);
         if (j <= M - 2) {
-            dt1 += pi * dh;
-            at1 += pi * ah;
+            dt1 = sel(j, dt1 + pi * dh, dt1);
+            at1 = sel(j, at1 + pi * ah, at1);
         }
         if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
@@ -364,16 +396,16 @@ __device__ __forceinline__ void shift_solve_recomp(const char *base, const Shift
         if ((j & 3) == 1) rows_group(e);
         const T2 abj = AB[j], cmj = CM[j];
         const T g = dev::recip(pivot(j, abj, cmj, chp));
-        e = (v[slot(j)] - abj.x * e) * g;
+        e = sel(j, (v[slot(j)] - abj.x * e) * g, e);
         v[slot(j)] = e;
-        chp = cmj.x * g;
+        chp = sel(j, cmj.x * g, chp);
         if (j % K == 0) ck[j / K - 1] = chp;
         if ((j & 3) == 0) __builtin_amdgcn_sched_barrier(0);
     }
     // backward, one segment at a time from the last: its c_j g_j recomputed
     // forward from the checkpoint, then x_j stored at once and, the walk
     // rolling on, the register refilled with the next tile's row M-1-j
-    int64_t xo = io.xo + (int64_t)(M - 1) * io.rs;
+    int64_t xo = io.xo + (int64_t)(cnt - 1) * io.rs;
     int64_t no = io.no;
     T xn = xld;
     if (io.valid) __builtin_nontemporal_store(xn, io.x + xo);
@@ -388,23 +420,23 @@ __device__ __forceinline__ void shift_solve_recomp(const char *base, const Shift
         for (int j = j0; j <= j1; ++j) {
             if (j > j0 && ((j - j0) & 3) == 0) rows_group(c);
             const T2 abj = AB[j], cmj = CM[j];
-            c = cmj.x * dev::recip(pivot(j, abj, cmj, c));
+            c = sel(j, cmj.x * dev::recip(pivot(j, abj, cmj, c)), c);
             chs[j - j0] = c;
         }
 #pragma unroll
         for (int j = j1; j >= j0; --j) {
-            T xj = v[slot(j)] - chs[j - j0] * xn;
+            T xj = sel(j, v[slot(j)] - chs[j - j0] * xn, xn);
             xj = opaque(xj);
-            xo = opaque(xo - io.rs);
-            if (io.valid) __builtin_nontemporal_store(xj, io.x + xo);
-            no = opaque(no + io.rs);
+            xo = opaque(xo - (have(j) ? io.rs : 0));
+            if (io.valid && have(j)) __builtin_nontemporal_store(xj, io.x + xo);
+            no = opaque(no + (have(M - 2 - j) ? io.rs : 0));
             v[slot(j)] = __builtin_nontemporal_load(io.d + no);
             xn = xj;
         }
         __builtin_amdgcn_sched_barrier(0);
     }
     if (io.valid) __builtin_nontemporal_store((T)xfd, io.x + io.xo);
-    v[slot(0)] = __builtin_nontemporal_load(io.d + (no + io.rs));
+    v[slot(0)] = __builtin_nontemporal_load(io.d + (no + (have(M - 2) ? io.rs : 0)));
 }
 
 // The lane's M rows of d (system base `sb` in elements, `valid` false past the
@@ -440,19 +472,22 @@ constexpr int shift_max_threads() { return (int)sizeof(T) * M >= 256 ? 512 : 102
 // otherwise each tile is loaded whole at its start.  RC (FP64, ROLL): the
 // solve that recomputes its pivots (shift_solve_recomp), in workgroups of up
 // to 1024 lanes.
-template <typename T, int M, bool ROLL, bool RC, int PQ>
+// UNEVEN (RC): partitions that do not fill their slots.
+template <typename T, int M, bool ROLL, bool RC, int PQ, bool UNEVEN>
 __global__ void __launch_bounds__((RC ? 1024 : shift_max_threads<T, M>()))
 k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, int32_t ntiles,
                int *err) {
     static_assert(!RC || (ROLL && std::is_same<T, double>::value), "RC: FP64, rolling walk");
+    static_assert(RC || !UNEVEN, "uneven partitions: the pivot-recomputing walk");
     extern __shared__ double lds[];
     char *base = reinterpret_cast<char *>(lds);
     const int tid = threadIdx.x;
     const int S = 1 << S_log2, P = 1 << P_log2;
     const int s = tid & (S - 1);
     const int p = tid >> S_log2;
-    const int r0 = p * M;
     const int64_t n = map.n, rs = map.row_stride;
+    const int nq = (int)n >> P_log2, nr = (int)n & (P - 1);
+    const int r0 = UNEVEN ? p * nq + (p < nr ? p : nr) : p * M;
     const int32_t nsys0 = (int32_t)map.nsys0;
     const int32_t nsys = (int32_t)map.nsys;
     const ShiftLds L = shift_layout(sizeof(T), M, P, S);
@@ -465,14 +500,23 @@ k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, 
     auto sbase = [&](const Walk &ww) {
         return (int64_t)ww.s0 * map.sys_stride0 + (int64_t)ww.s1 * map.sys_stride1;
     };
-    const int nrow = (int)(n - r0 < 0 ? 0 : (n - r0 > M ? M : n - r0));
+    const int nrow = UNEVEN ? nq + (p < nr ? 1 : 0) : (int)(n - r0 < 0 ? 0 : (n - r0 > M ? M : n - r0));
     bool bad = false;
-    build_rows<T>(coef, n, M, P, base, L);
+    build_rows<T, UNEVEN>(coef, n, M, P, base, L);
     T v[M];
     int64_t b = sbase(w);
     bool ok = w.k < nsys;
     T sh = SH[ok ? w.k : 0];
-    load_lane<T, M>(d, b, ok, rs, r0, n, v);
+    if constexpr (UNEVEN) {
+        int64_t q = (ok ? b : 0) + (int64_t)r0 * rs;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            v[j] = __builtin_nontemporal_load(d + q);
+            q += j < M - 1 - kSlack || j < nrow - 1 ? rs : 0;
+        }
+    } else {
+        load_lane<T, M>(d, b, ok, rs, r0, n, v);
+    }
     if constexpr (ROLL) {
         // one tile in layout F; the next tile's rows arrive in layout 1 - F
         auto one = [&](auto layout) {
@@ -487,10 +531,10 @@ k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, 
             io.xo = b + (int64_t)r0 * rs;
             io.no = (nok ? nb : 0) + (int64_t)r0 * rs;
             io.rs = rs;
-            io.nrow = M;
+            io.nrow = UNEVEN ? nrow : M;
             io.valid = ok;
             if constexpr (RC)
-                shift_solve_recomp<M, F, kRecompSeg, PQ>(base, L, S, s, p, P, P_log2, sh, v, io, bad);
+                shift_solve_recomp<M, F, kRecompSeg, PQ, UNEVEN>(base, L, S, s, p, P, P_log2, sh, v, io, bad);
             else
                 shift_solve<T, M, F, true, PQ>(base, L, S, s, p, P, P_log2, sh, v, io, bad);
             b = nb;
@@ -903,7 +947,7 @@ int64_t resident_of(K kernel, int threads, size_t lds) {
     return (int64_t)cus * per_cu;
 }
 
-template <typename T, int M, bool ROLL, bool RC, int PQ>
+template <typename T, int M, bool ROLL, bool RC, int PQ, bool UNEVEN = false>
 hipError_t launch_tq(const SysMap &map, const Coef &coef, const TileShape &sh, const void *d, void *x,
                      int *err, hipStream_t st) {
     const int S = 1 << sh.S_log2;
@@ -911,24 +955,24 @@ hipError_t launch_tq(const SysMap &map, const Coef &coef, const TileShape &sh, c
     const size_t lds = shift_layout(sizeof(T), M, sh.P, S).end;
     const int64_t ntiles = (map.nsys + S - 1) / S;
     if (ntiles == 0) return hipSuccess;
-    const int64_t resident = resident_of(k_shift_stream<T, M, ROLL, RC, PQ>, sh.threads(), lds);
+    const int64_t resident = resident_of(k_shift_stream<T, M, ROLL, RC, PQ, UNEVEN>, sh.threads(), lds);
     if (resident < 1) return hipErrorInvalidConfiguration;
     const int64_t grid = ntiles < resident ? ntiles : resident;
-    hipLaunchKernelGGL((k_shift_stream<T, M, ROLL, RC, PQ>), dim3((unsigned)grid), dim3(sh.threads()), lds,
+    hipLaunchKernelGGL((k_shift_stream<T, M, ROLL, RC, PQ, UNEVEN>), dim3((unsigned)grid), dim3(sh.threads()), lds,
                        st, map, coef, (const T *)d, (T *)x, sh.S_log2, P_log2, (int32_t)ntiles, err);
     return hipGetLastError();
 }
 
 // 16 and 32 partitions take the DPP form of Stage B (its partition count
 // fixed at compile time), other counts the wavefront-shuffle form.
-template <typename T, int M, bool ROLL, bool RC = false>
+template <typename T, int M, bool ROLL, bool RC = false, bool UNEVEN = false>
 hipError_t launch_t(const SysMap &map, const Coef &coef, const TileShape &sh, const void *d, void *x,
                     int *err, hipStream_t st) {
     switch (sh.P) {
-        case 16: return launch_tq<T, M, ROLL, RC, 2>(map, coef, sh, d, x, err, st);
-        case 32: return launch_tq<T, M, ROLL, RC, 4>(map, coef, sh, d, x, err, st);
+        case 16: return launch_tq<T, M, ROLL, RC, 2, UNEVEN>(map, coef, sh, d, x, err, st);
+        case 32: return launch_tq<T, M, ROLL, RC, 4, UNEVEN>(map, coef, sh, d, x, err, st);
     }
-    return launch_tq<T, M, ROLL, RC, 0>(map, coef, sh, d, x, err, st);
+    return launch_tq<T, M, ROLL, RC, 0, UNEVEN>(map, coef, sh, d, x, err, st);
 }
 
 template <typename T, int M>
@@ -936,7 +980,11 @@ hipError_t launch_m(const SysMap &map, const Coef &coef, const TileShape &sh, co
                     int *err, hipStream_t st) {
     // kernel 3 rolls the walk on when the partitions cover n exactly; kernel 4
     // (and padded lengths) load each tile at its start; kernel 7 (FP64, P*M =
-    // n) recomputes its pivots
+    // n or uneven partitions) recomputes its pivots
+    if constexpr (std::is_same<T, double>::value && M % 4 == 0 && M >= 20) {
+        if (sh.kernel == 7 && shift_uneven(map.n, sh))
+            return launch_t<T, M, true, true, true>(map, coef, sh, d, x, err, st);
+    }
     if constexpr (std::is_same<T, double>::value && (M == 16 || M == 32)) {
         if (sh.kernel == 7) {
             if ((int64_t)sh.P * M != map.n) return hipErrorInvalidValue;
@@ -944,9 +992,12 @@ hipError_t launch_m(const SysMap &map, const Coef &coef, const TileShape &sh, co
         }
     }
     if (sh.kernel == 7) return hipErrorInvalidValue;
-    const bool roll = sh.kernel == 3 && (int64_t)sh.P * M == map.n;
-    return roll ? launch_t<T, M, true>(map, coef, sh, d, x, err, st)
-                : launch_t<T, M, false>(map, coef, sh, d, x, err, st);
+    if constexpr (M == 8 || M == 16 || M == 32) {
+        const bool roll = sh.kernel == 3 && (int64_t)sh.P * M == map.n;
+        return roll ? launch_t<T, M, true>(map, coef, sh, d, x, err, st)
+                    : launch_t<T, M, false>(map, coef, sh, d, x, err, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int M, bool FULL, int PQ>
@@ -983,6 +1034,14 @@ hipError_t launch_refine_m(const SysMap &map, const Coef &coef, const TileShape 
 size_t shift_lds_bytes(int dtype, const TileShape &sh) {
     const size_t esz = dtype == TDMA_F64 ? 8 : 4;
     return shift_layout(esz, sh.M, sh.P, 1 << sh.S_log2).end;
+}
+
+// Kernel 7 on partitions of floor(n/P) and floor(n/P) + 1 rows that leave at
+// most kSlack of M = 20, 24, 28 or 32 slots empty.
+bool shift_uneven(int64_t n, const TileShape &sh) {
+    const int64_t slots = (int64_t)sh.P * sh.M;
+    return sh.kernel == 7 && sh.M >= 20 && sh.M <= 32 && sh.M % 4 == 0 && n <= slots &&
+           (sh.M < 32 || n < slots) && n / sh.P >= sh.M - kSlack;
 }
 
 bool shift_supported(int dtype, const TileShape &sh) {
@@ -1031,9 +1090,18 @@ hipError_t launch_shift_refine(const SysMap &map, const Coef &coef, const TileSh
 
 hipError_t launch_shift(int dtype, const SysMap &map, const Coef &coef, const TileShape &sh,
                         const void *d, void *x, int *err, hipStream_t st) {
-    if (!shift_supported(dtype, sh) || !shift_layout_ok(map, sh) || coef.mode != TDMA_COEF_SHARED ||
+    TileShape chk = sh;
+    const bool uneven = dtype == TDMA_F64 && shift_uneven(map.n, sh);
+    if (uneven) chk.M = 32;   // lanes and LDS of the fullest slots
+    if (!shift_supported(dtype, chk) || !shift_layout_ok(map, sh) || coef.mode != TDMA_COEF_SHARED ||
         coef.shift == nullptr)
         return hipErrorInvalidValue;
+    if (uneven) {
+        if (sh.M == 20) return launch_m<double, 20>(map, coef, sh, d, x, err, st);
+        if (sh.M == 24) return launch_m<double, 24>(map, coef, sh, d, x, err, st);
+        if (sh.M == 28) return launch_m<double, 28>(map, coef, sh, d, x, err, st);
+        return launch_m<double, 32>(map, coef, sh, d, x, err, st);
+    }
     if (dtype == TDMA_F64) {
         if (sh.M == 8) return launch_m<double, 8>(map, coef, sh, d, x, err, st);
         if (sh.M == 16) return launch_m<double, 16>(map, coef, sh, d, x, err, st);

@@ -77,6 +77,7 @@ hipError_t launch_copy_streamed(int dtype, const SysMap &map, const TileShape &s
 
 // shared operator with a per-system shift, strided layouts (shifted.hip)
 bool shift_supported(int dtype, const TileShape &shape);
+bool shift_uneven(int64_t n, const TileShape &shape);
 bool shift_layout_ok(const SysMap &map, const TileShape &shape);
 size_t shift_lds_bytes(int dtype, const TileShape &shape);
 hipError_t launch_shift(int dtype, const SysMap &map, const Coef &coef, const TileShape &shape,
