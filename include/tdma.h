@@ -195,8 +195,9 @@ int tdma_solve_pdd(const tdma_layout *layout, const tdma_coeffs *coeffs, int dty
  * unused); shift is a HOST array of ny * (nx/2 + 1) values, mode (kx, ky) at
  * ky * (nx/2 + 1) + kx (the negated modified wavenumber, so that the mode's
  * operator is a, b + shift, c).  The plan owns two half-spectrum buffers of
- * nz * ny * (nx/2 + 1) complex doubles and the hipFFT plans; it is made on
- * the current device.  nz <= 1024.  Errors: EINVAL (arguments), EUNSUPPORTED
+ * nz * ny * (nx/2 + 1) complex doubles (rows padded to whole lines where ny is
+ * a power of two from 64 to 512) and the hipFFT plans; it is made on the
+ * current device.  nz <= 1024.  Errors: EINVAL (arguments), EUNSUPPORTED
  * (nz > 1024), ENOMEM, EHIP (hipFFT).
  * tdma_poisson_solve: q and phi are DEVICE arrays of nx*ny*nz doubles; q may
  * be used as scratch by the forward transform (its content afterwards is

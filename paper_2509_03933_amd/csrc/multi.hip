@@ -230,10 +230,14 @@ inline size_t multi_lds_bytes(size_t esz, int S, int P, int M, int NR) {
 // the same memory channels, scattered ones do not.  With spread == 0 the
 // order is XCD-aware (dev::xcd_tile), for tile rows narrower than a line.
 // x may alias d: a block reads all of its tile before it writes any of it.
+// pin (x not d): system 0 has an operator of its own, the tables a, b, c of n
+// rows at pin, without a shift; one block more than the tiles solves it, and
+// the block whose tile holds system 0 leaves it out (a launch of its own for
+// that one system took 12 us of a small FFT-Poisson step's 40).
 template <typename T, int M, int NR, bool SHIFT, bool VEC>
 __global__ void __launch_bounds__(512)
 k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2, int P_log2,
-        int64_t spread, int *err) {
+        int64_t spread, const T *pin, int *err) {
     static_assert(!VEC || NR == 2, "vector form moves two right-hand sides");
     extern __shared__ double lds[];
     const int tid = threadIdx.x;
@@ -243,10 +247,17 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
     const int p = tid >> S_log2;
     const int r0 = p * M;
     const int R = P * M;
-    const int64_t nb = gridDim.x;
-    const int64_t k0 = (spread > 0 ? ((int64_t)blockIdx.x * spread) % nb
-                                    : dev::xcd_tile(blockIdx.x, nb)) << S_log2;
-    const LaneSys sys = dev::lane_system(map, k0 + s);
+    const int64_t nb = (int64_t)gridDim.x - (pin ? 1 : 0);
+    const bool pinned = pin && (int64_t)blockIdx.x == nb;
+    const int64_t k0 = pinned ? 0
+                       : (spread > 0 ? ((int64_t)blockIdx.x * spread) % nb
+                                     : dev::xcd_tile(blockIdx.x, nb)) << S_log2;
+    if (pinned) {
+        coef.a = pin;
+        coef.b = pin + map.n;
+        coef.c = pin + 2 * map.n;
+    }
+    const LaneSys sys = dev::lane_system(map, pinned && s > 0 ? map.nsys : k0 + s);
     const int rows_here = (int)(sys.nrows - r0 < 0 ? 0 : (sys.nrows - r0 > M ? M : sys.nrows - r0));
     T *CO = reinterpret_cast<T *>(lds);
 
@@ -281,7 +292,7 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
     T sh = T(0);
     if constexpr (SHIFT) {
         sh = ((const T *)coef.shift)[sys.valid ? sys.id : 0];
-        if (!sys.valid) sh = T(0);
+        if (!sys.valid || pinned) sh = T(0);
     }
     dev::rows_commit<T, CR, T, 4>(CO, coef, map.n, R, rr);
 #pragma unroll
@@ -307,9 +318,10 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
     }
 
     const int64_t off0 = sys.base + (int64_t)r0 * rs;
+    const int rows_out = pin && !pinned && sys.id == 0 ? 0 : rows_here;
 #pragma unroll
     for (int j = 0; j < M; ++j)
-        if (j < rows_here) {
+        if (j < rows_out) {
             const int64_t idx = off0 + j * rs;
             if constexpr (VEC) {
                 typedef T T2 __attribute__((ext_vector_type(2)));
@@ -345,7 +357,7 @@ int64_t spread_stride(int64_t nb) {
 
 template <typename T, int M, int NR, bool SHIFT, bool VEC>
 hipError_t launch_t(const SysMap &map, const Coef &coef, const MultiShape &sh, int64_t rhs_stride,
-                    const void *d, void *x, int *err, hipStream_t st) {
+                    const void *d, void *x, const void *pin, int *err, hipStream_t st) {
     const int64_t S = (int64_t)1 << sh.S_log2;
     const int64_t blocks = (map.nsys + S - 1) / S;
     if (blocks == 0) return hipSuccess;
@@ -353,20 +365,20 @@ hipError_t launch_t(const SysMap &map, const Coef &coef, const MultiShape &sh, i
     // full 128-byte tile rows: scattered tile order; narrower: XCD-aware
     const int64_t row_bytes = S * (int64_t)sizeof(T) * (VEC ? 2 : 1);
     const int64_t spread = row_bytes >= 128 ? spread_stride(blocks) : 0;
-    hipLaunchKernelGGL((k_multi<T, M, NR, SHIFT, VEC>), dim3((unsigned)blocks),
+    hipLaunchKernelGGL((k_multi<T, M, NR, SHIFT, VEC>), dim3((unsigned)(blocks + (pin ? 1 : 0))),
                        dim3((unsigned)(S << sh.P_log2)), lds, st, map, coef, (const T *)d, (T *)x,
-                       rhs_stride, sh.S_log2, sh.P_log2, spread, err);
+                       rhs_stride, sh.S_log2, sh.P_log2, spread, (const T *)pin, err);
     return hipGetLastError();
 }
 
 template <typename T, int M>
 hipError_t launch_group(const SysMap &map, const Coef &coef, const MultiShape &sh, int nr,
-                        bool vec, int64_t rhs_stride, const void *d, void *x, int *err,
-                        hipStream_t st) {
+                        bool vec, int64_t rhs_stride, const void *d, void *x, const void *pin,
+                        int *err, hipStream_t st) {
     const bool shift = coef.shift != nullptr;
 #define TDMA_MULTI(NR, SH, V)                                                                   \
     if (nr == NR && shift == SH && vec == V)                                                    \
-        return launch_t<T, M, NR, SH, V>(map, coef, sh, rhs_stride, d, x, err, st);
+        return launch_t<T, M, NR, SH, V>(map, coef, sh, rhs_stride, d, x, pin, err, st);
     TDMA_MULTI(2, true, true)
     TDMA_MULTI(2, false, true)
     TDMA_MULTI(2, true, false)
@@ -399,7 +411,7 @@ size_t multi_lds(int dtype, const MultiShape &sh, int nr) {
 
 hipError_t launch_multi(int dtype, const SysMap &map, const Coef &coef, const MultiShape &sh,
                         int nrhs, int64_t rhs_stride, bool vec, const void *d, void *x, int *err,
-                        hipStream_t st) {
+                        hipStream_t st, const void *pin) {
     const size_t esz = dtype == TDMA_F64 ? 8 : 4;
     // groups of two right-hand sides, then a single one when nrhs is odd
     for (int r = 0; r < nrhs;) {
@@ -409,9 +421,9 @@ hipError_t launch_multi(int dtype, const SysMap &map, const Coef &coef, const Mu
         const bool v = vec && nr == 2;
         hipError_t e;
         if (dtype == TDMA_F64 && sh.M == 16)
-            e = launch_group<double, 16>(map, coef, sh, nr, v, rhs_stride, dg, xg, err, st);
+            e = launch_group<double, 16>(map, coef, sh, nr, v, rhs_stride, dg, xg, pin, err, st);
         else if (dtype == TDMA_F32 && sh.M == 32)
-            e = launch_group<float, 32>(map, coef, sh, nr, v, rhs_stride, dg, xg, err, st);
+            e = launch_group<float, 32>(map, coef, sh, nr, v, rhs_stride, dg, xg, pin, err, st);
         else
             e = hipErrorInvalidValue;
         if (e != hipSuccess) return e;

@@ -7,17 +7,20 @@
 // sides), and the inverse 2-D FFT returns the field.  The inverse transform
 // is unnormalised, so the operator tables are stored multiplied by nx*ny
 // (x = (N A)^-1 d = A^-1 d / N): no scaling pass.  Mode (0, 0) is singular
-// with Neumann walls; it is solved separately with its row 0 replaced by
-// x_0 = d_0 (the bulk call gives it a placeholder shift and its result is
-// overwritten).
+// with Neumann walls; it is solved with its row 0 replaced by x_0 = d_0, by a
+// block of its own in the same launch (k_multi's pin).
 #include <hipfft/hipfft.h>
 
+#include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "api_internal.h"
 
 struct tdma_poisson {
     int nx = 0, ny = 0, nz = 0, h = 0;
+    int hp = 0;                            // elements between rows of a half spectrum (>= h)
+    int64_t plane = 0;                     // elements between its z planes
     int dev = 0;
     hipfftHandle fwd = 0, inv = 0;
     bool has_fwd = false, has_inv = false;
@@ -68,13 +71,24 @@ int tdma_poisson_create(int nx, int ny, int nz, const double *a, const double *b
     pl->ny = ny;
     pl->nz = nz;
     pl->h = nx / 2 + 1;
+    // ny a power of two from 64 to 512: the library's column transforms work on
+    // groups of columns narrower than a 128-byte line, so rows of the spectrum
+    // that start on a line (and planes an odd number of 4 KB pages apart, whose
+    // rows the z solve finds on different channels) spare them the shared
+    // lines: 512^3 column passes 721 -> 479 us, step 3157 -> 2665; 256^3 419 ->
+    // 341; 300 x 256 x 256 473 -> 411.  Other lengths lose (320^3 830 -> 862),
+    // and so do columns of 1024 (1024 x 1024 x 100 3129 -> 3250).
+    const bool lines = ny >= 64 && ny <= 512 && (ny & (ny - 1)) == 0 && pl->h >= 16;
+    pl->hp = lines ? (pl->h + 7) / 8 * 8 : pl->h;
     hipError_t e = hipGetDevice(&pl->dev);
     if (e != hipSuccess) { delete pl; return hip_fail(e, "hipGetDevice"); }
     const int64_t modes = (int64_t)ny * pl->h;
     const double N = (double)nx * (double)ny;
     // tables scaled by N; the pinned set has row 0 = (0, N, 0); mode (0, 0)
     // takes another mode's shift in the bulk call (a placeholder)
-    std::vector<double> t(6 * (size_t)nz + (size_t)modes);
+    // (the padding columns' lines are solved too, with a mode's shift)
+    const int64_t zlines = (int64_t)ny * pl->hp;
+    std::vector<double> t(6 * (size_t)nz + (size_t)zlines);
     for (int k = 0; k < nz; ++k) {
         t[k] = N * a[k];
         t[nz + k] = N * b[k];
@@ -86,10 +100,15 @@ int tdma_poisson_create(int nx, int ny, int nz, const double *a, const double *b
     t[3 * nz] = 0.0;
     t[4 * nz] = N;
     t[5 * nz] = 0.0;
-    for (int64_t m = 0; m < modes; ++m) t[6 * (size_t)nz + m] = N * shift[m];
-    if (modes > 1) t[6 * (size_t)nz] = t[6 * (size_t)nz + 1];
+    for (int64_t ky = 0; ky < ny; ++ky)
+        for (int64_t kx = 0; kx < pl->hp; ++kx)
+            t[6 * (size_t)nz + ky * pl->hp + kx] = N * shift[ky * pl->h + std::min<int64_t>(kx, pl->h - 1)];
+    if (modes > 1) t[6 * (size_t)nz] = N * (pl->h > 1 ? shift[1] : shift[pl->h]);
     else t[6 * (size_t)nz] = -N;
-    const size_t spec = (size_t)nz * modes * 2 * sizeof(double);
+    int64_t plane = (int64_t)ny * pl->hp;
+    if (lines) plane = ((plane + 255) / 256 | 1) * 256;
+    pl->plane = plane;
+    const size_t spec = (size_t)nz * plane * 2 * sizeof(double);
     if (hipMalloc(&pl->tab, t.size() * sizeof(double)) != hipSuccess ||
         hipMalloc(&pl->W1, spec) != hipSuccess || hipMalloc(&pl->W2, spec) != hipSuccess) {
         release(pl);
@@ -98,11 +117,12 @@ int tdma_poisson_create(int nx, int ny, int nz, const double *a, const double *b
     e = hipMemcpy(pl->tab, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e != hipSuccess) { release(pl); return hip_fail(e, "upload of the Poisson tables"); }
     int n[2] = {ny, nx};
-    hipfftResult r = hipfftPlanMany(&pl->fwd, 2, n, nullptr, 1, nx * ny, nullptr, 1, (int)modes,
+    int real_rows[2] = {ny, nx}, spec_rows[2] = {ny, pl->hp};
+    hipfftResult r = hipfftPlanMany(&pl->fwd, 2, n, real_rows, 1, nx * ny, spec_rows, 1, (int)plane,
                                     HIPFFT_D2Z, nz);
     if (r != HIPFFT_SUCCESS) { release(pl); return fft_fail(r, "forward plan"); }
     pl->has_fwd = true;
-    r = hipfftPlanMany(&pl->inv, 2, n, nullptr, 1, (int)modes, nullptr, 1, nx * ny, HIPFFT_Z2D, nz);
+    r = hipfftPlanMany(&pl->inv, 2, n, spec_rows, 1, (int)plane, real_rows, 1, nx * ny, HIPFFT_Z2D, nz);
     if (r != HIPFFT_SUCCESS) { release(pl); return fft_fail(r, "inverse plan"); }
     pl->has_inv = true;
     *out = pl;
@@ -118,38 +138,37 @@ int tdma_poisson_solve(tdma_poisson *pl, const double *q, double *phi, void *str
     if (cur != pl->dev)
         return fail(TDMA_EINVAL, "the plan was made on device %d, device %d is current", pl->dev, cur);
     const hipStream_t st = (hipStream_t)stream;
-    const int nz = pl->nz, h = pl->h;
+    const int nz = pl->nz;
     hipfftResult r = hipfftSetStream(pl->fwd, st);
     if (r == HIPFFT_SUCCESS)
         r = hipfftExecD2Z(pl->fwd, const_cast<double *>(q), reinterpret_cast<hipfftDoubleComplex *>(pl->W1));
     if (r != HIPFFT_SUCCESS) return fft_fail(r, "forward transform");
     tdma_layout L{};
     L.n = nz;
-    L.nsys0 = h;
+    L.nsys0 = pl->hp;
     L.nsys1 = pl->ny;
-    L.row_stride = 2 * (int64_t)pl->ny * h;
+    L.row_stride = 2 * pl->plane;
     L.sys_stride0 = 2;
-    L.sys_stride1 = 2 * (int64_t)h;
+    L.sys_stride1 = 2 * (int64_t)pl->hp;
     L.offsets = nullptr;
-    tdma_coeffs C{};
+    Coef C{};
     C.mode = TDMA_COEF_SHARED;
     C.a = pl->tab;
     C.b = pl->tab + nz;
     C.c = pl->tab + 2 * nz;
-    C.b_shift = pl->tab + 6 * (size_t)nz;
-    int rc = tdma_solve_multi(&L, &C, TDMA_F64, 2, 1, pl->W1, pl->W2, stream);
-    if (rc != TDMA_OK) return rc;
-    tdma_layout L0 = L;
-    L0.nsys0 = 1;
-    L0.nsys1 = 1;
-    tdma_coeffs C0{};
-    C0.mode = TDMA_COEF_SHARED;
-    C0.a = pl->tab + 3 * nz;
-    C0.b = pl->tab + 4 * nz;
-    C0.c = pl->tab + 5 * nz;
-    C0.b_shift = nullptr;
-    rc = tdma_solve_multi(&L0, &C0, TDMA_F64, 2, 1, pl->W1, pl->W2, stream);
-    if (rc != TDMA_OK) return rc;
+    C.shift = pl->tab + 6 * (size_t)nz;
+    MultiShape sh;
+    if (!multi_shape(TDMA_F64, nz, (int64_t)pl->hp * pl->ny, &sh))
+        return fail(TDMA_EUNSUPPORTED, "nz = %d is longer than the z solve holds", nz);
+    {
+        DeviceCtx *ctx = nullptr;
+        const int rc = get_ctx(&ctx);
+        if (rc != TDMA_OK) return rc;
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        const hipError_t le = launch_multi(TDMA_F64, make_map(&L), C, sh, 2, 1, true, pl->W1, pl->W2,
+                                           ctx->d_err, st, pl->tab + 3 * (size_t)nz);
+        if (le != hipSuccess) return hip_fail(le, "z solve launch");
+    }
     clear_error();
     r = hipfftSetStream(pl->inv, st);
     if (r == HIPFFT_SUCCESS)

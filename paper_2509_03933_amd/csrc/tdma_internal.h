@@ -116,9 +116,10 @@ struct MultiShape {
 // built-in shape for systems of n rows (false: n needs more than 64 partitions)
 bool multi_shape(int dtype, int64_t n, int64_t nsys, MultiShape *out);
 size_t multi_lds(int dtype, const MultiShape &shape, int nr);
-// vec: two right-hand sides adjacent (rhs_stride 1) and pair-aligned
+// vec: two right-hand sides adjacent (rhs_stride 1) and pair-aligned; pin: the
+// operator of system 0 alone, see k_multi
 hipError_t launch_multi(int dtype, const SysMap &map, const Coef &coef, const MultiShape &shape,
                         int nrhs, int64_t rhs_stride, bool vec, const void *d, void *x,
-                        int *err_flag, hipStream_t stream);
+                        int *err_flag, hipStream_t stream, const void *pin = nullptr);
 
 }  // namespace tdma
