@@ -64,7 +64,11 @@ hipError_t launch_m(const SysMap &map, const Coef &coef, const TileShape &sh, co
     const bool shift = coef.shift != nullptr;
     const int dtype = sizeof(T) == 8 ? TDMA_F64 : TDMA_F32;
     const size_t lds_co = fused_lds_bytes(dtype, sh, true);
-    const bool co = !like_d && lds_co <= kCoLdsLimit;
+    // (the two-level solve's spare slots, at most 11 KB where the limit is near,
+    // don't count: two blocks fit a CU with them too)
+    const int S = 1 << sh.S_log2;
+    const size_t spare = sh.contig ? 0 : dev::iface_lds_bytes(S, sh.P) - dev::pcr_lds_bytes(S, sh.P);
+    const bool co = !like_d && lds_co - spare <= kCoLdsLimit;
     const size_t lds = co ? lds_co : fused_lds_bytes(dtype, sh, false);
 #define TDMA_DISPATCH(LD, SH, CT, C)                                                         \
     if (like_d == LD && shift == SH && sh.contig == CT && co == C)                           \

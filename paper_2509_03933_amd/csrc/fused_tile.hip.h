@@ -110,7 +110,7 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
         const int pitch = P * (M + 1) + 1;
         T *stg = reinterpret_cast<T *>(lds);
         const size_t stg_bytes = ((size_t)S * pitch * sizeof(T) + 15) & ~(size_t)15;
-        const size_t pcr_bytes = dev::pcr_lds_bytes(S, P);
+        const size_t pcr_bytes = dev::iface_lds_bytes(S, P);
         TileSysLds *tsys = reinterpret_cast<TileSysLds *>(
             reinterpret_cast<char *>(lds) + (stg_bytes > pcr_bytes ? stg_bytes : pcr_bytes));
         if (tid < S) {
@@ -179,7 +179,7 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
         const int pitch = P * (M + 1) + 1;
         T *stg = reinterpret_cast<T *>(lds);
         const size_t stg_bytes = ((size_t)S * pitch * sizeof(T) + 15) & ~(size_t)15;
-        const size_t pcr_bytes = dev::pcr_lds_bytes(S, P);
+        const size_t pcr_bytes = dev::iface_lds_bytes(S, P);
         TileSysLds *tsys = reinterpret_cast<TileSysLds *>(
             reinterpret_cast<char *>(lds) + (stg_bytes > pcr_bytes ? stg_bytes : pcr_bytes));
         dev::stage_out_sw<T, M>(stg, tsys, x, S, R, pitch, 1.0f / (float)R, s, p, dv);
@@ -195,7 +195,7 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
 // P*(M+1)+1), the shared-operator tile with pitch P*M+1.
 __host__ __device__ inline size_t fused_region0(size_t esz, int S, int P, int M, bool contig,
                                                 bool sw = false) {
-    const size_t pcr = dev::pcr_lds_bytes(S, P);
+    const size_t pcr = dev::iface_lds_bytes(S, P);
     if (!contig) return pcr;
     const size_t pitch = sw ? (size_t)P * (M + 1) + 1 : (size_t)P * M + 1;
     const size_t stg = ((size_t)S * pitch * esz + 15) & ~(size_t)15;

@@ -112,11 +112,15 @@ __device__ __forceinline__ LaneSys lane_system(const SysMap &m, int64_t k) {
 __host__ __device__ constexpr int two_level_rows(int P) { return (2 * P + 63) / 64; }
 __host__ __device__ constexpr int two_level_pitch(int P) { return 64 * (two_level_rows(P) + 1); }
 
-// LDS bytes of Stage B for S systems x P partitions: three arrays (a, c, d)
-// of 2P rows per system plus one pad row (the PCR variants), or the two-level
-// solve's slots above 64 partitions.
+// LDS bytes of Stage B for S systems x P partitions in its PCR variants: three
+// arrays (a, c, d) of 2P rows per system plus one pad row.
 __host__ __device__ constexpr size_t pcr_lds_bytes(int S, int P) {
-    return (size_t)3 * S * (P > 64 ? two_level_pitch(P) : 2 * P + 1) * sizeof(double);
+    return (size_t)3 * S * (2 * P + 1) * sizeof(double);
+}
+
+// The same for the kernels that solve above 64 partitions in two levels.
+__host__ __device__ constexpr size_t iface_lds_bytes(int S, int P) {
+    return P > 64 ? (size_t)3 * S * two_level_pitch(P) * sizeof(double) : pcr_lds_bytes(S, P);
 }
 
 // Interface rows of one partition (unit diagonal): first row couples
