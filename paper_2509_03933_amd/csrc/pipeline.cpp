@@ -42,13 +42,33 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
     for (int i = 0; i < nslots; ++i)
         (void)stage_ws(dtype, coef, n, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
 
-    // one batch has nothing to overlap with: its three stages run on the
-    // caller's stream, with no fork and join (four streams and eight event
-    // operations otherwise)
+    // One batch has nothing to overlap with: its three stages run in sequence on
+    // the library's first stream, with one fork and join.  Not on the caller's
+    // own stream: the workspace is one per device, and the one-batch calls of
+    // several streams follow one another on that stream.  (A caller that records
+    // a graph has them on its own stream, in the graph.)
     if (nbatches == 1) {
-        hipError_t e = launch_stage_a(dtype, map, coef, d, slots[0], 0, nsys, P, ctx->d_err, caller);
-        if (e == hipSuccess) e = launch_stage_b(slots[0], nsys, P, ctx->d_err, caller);
-        if (e == hipSuccess) e = launch_stage_c(dtype, map, coef, d, x, slots[0], 0, nsys, P, caller);
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(caller, &cs);
+        if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+        const bool own = cs == hipStreamCaptureStatusNone;
+        hipStream_t q = caller, *lib = nullptr;
+        hipEvent_t *ev = nullptr;
+        if (own) {
+            rc = ctx->get_streams(1, &lib);
+            if (rc == TDMA_OK) rc = ctx->get_events(2, &ev);
+            if (rc != TDMA_OK) return rc;
+            q = lib[0];
+            e = hipEventRecord(ev[0], caller);
+            if (e == hipSuccess) e = hipStreamWaitEvent(q, ev[0], 0);
+        }
+        if (e == hipSuccess) e = launch_stage_a(dtype, map, coef, d, slots[0], 0, nsys, P, ctx->d_err, q);
+        if (e == hipSuccess) e = launch_stage_b(slots[0], nsys, P, ctx->d_err, q);
+        if (e == hipSuccess) e = launch_stage_c(dtype, map, coef, d, x, slots[0], 0, nsys, P, q);
+        if (own && e == hipSuccess) {
+            e = hipEventRecord(ev[1], q);
+            if (e == hipSuccess) e = hipStreamWaitEvent(caller, ev[1], 0);
+        }
         return e == hipSuccess ? TDMA_OK : hip_fail(e, "pipeline launch");
     }
 
