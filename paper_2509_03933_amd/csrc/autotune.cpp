@@ -348,12 +348,12 @@ int tdma_autotune(const tdma_layout *layout, const tdma_coeffs *coeffs, int dtyp
             const int K = (int)std::min<int64_t>(kTuneStreams, nb);
             // K batch workspaces (the layout of one pipeline slot each)
             std::vector<StageWs> sl(K);
-            const size_t slot_bytes = stage_ws(dtype, coef, layout->n, s, P, nullptr, &sl[0]);
+            const size_t slot_bytes = stage_ws(dtype, map, coef, s, P, nullptr, &sl[0]);
             void *ws = nullptr;
             rc = ctx->workspace(4, slot_bytes * K, &ws);
             if (rc != TDMA_OK) return rc;
             for (int i = 0; i < K; ++i)
-                (void)stage_ws(dtype, coef, layout->n, s, P, (char *)ws + slot_bytes * i, &sl[i]);
+                (void)stage_ws(dtype, map, coef, s, P, (char *)ws + slot_bytes * i, &sl[i]);
             // every repetition takes other batches (full ones, so each stage
             // reads what the previous stage wrote for it): a batch's data is
             // not left in the caches by the previous repetition

@@ -5,17 +5,19 @@
 namespace tdma {
 
 // Workspace of one batch: the recurrence states Stage A keeps for Stage C
-// (nseg per partition), the reduced rows, the interface solution and the
-// scratch of the sequential Stage B.
+// (nseg per partition; keep_rows: of every row), the reduced rows, the
+// interface solution and the scratch of the sequential Stage B.
 struct StageWs {
     void *ws_d = nullptr, *ws_a = nullptr, *ws_c = nullptr;
     double *red = nullptr, *X = nullptr, *scratch = nullptr;
     int nseg = 0;
+    bool keep_rows = false;
 };
 
-// Bytes of the workspace for `batch` systems of n rows in P partitions;
+// Bytes of the workspace for `batch` of the map's systems in P partitions;
 // with mem, `out` points into it (mem null: the size alone).
-size_t stage_ws(int dtype, const Coef &coef, int64_t n, int64_t batch, int P, void *mem, StageWs *out);
+size_t stage_ws(int dtype, const SysMap &map, const Coef &coef, int64_t batch, int P, void *mem,
+                StageWs *out);
 
 hipError_t launch_stage_a(int dtype, const SysMap &map, const Coef &coef, const void *d,
                           const StageWs &w, int64_t k_begin, int64_t nb, int P, int *err,

@@ -6,7 +6,7 @@
 //   row-1 spike into a forward sum.  It writes the partition's two
 //   unit-diagonal interface equations (6 values) to the reduced buffer, and
 //   the recurrence's state (d^, a^, c^) at the first row of every segment of
-//   kSeg interior rows to a workspace.
+//   kSeg interior rows to a workspace (k_stage_a_rows: of every interior row).
 // Stage B (k_stage_b_pcr, k_stage_b_seq): the 2P-row interface system of every system of the
 //   batch, FP64; parallel cyclic reduction across P consecutive lanes with
 //   wavefront shuffles (P a power of two <= 64), otherwise one lane per system
@@ -17,7 +17,8 @@
 //   a^, c^), into registers, and then backwards x_{m-1} and x_0 being
 //   interface unknowns, x_j = d^_j - a^_j x_0 - c^_j x_{j+1}.  A segment's rows
 //   are read before any of them is written, and a lane reads only rows that
-//   it alone writes, so x may alias d.
+//   it alone writes, so x may alias d.  k_stage_c_rows walks the partition
+//   backwards over the kept d^, a^, c^ of every row instead.
 //
 // HBM-bound.  Reading the rows twice costs less than keeping their factors:
 // per unknown (FP64, per-row coefficients) A reads 32 B, C reads 30 and
@@ -25,6 +26,12 @@
 // with every row's d^, a^, c^ written by A and read by C (shared operator 25
 // against 32, with a shift 27 against 64), and the workspace is a sixteenth.
 // 131,072 per-row lines of 2048 rows (P = 8): 4.77 -> 3.97 ms (73 B: 4.9 TB/s).
+// That holds where the lanes of a wavefront read adjacent elements.  Where they
+// do not (contiguous rows: adjacent lanes are n elements apart, each row's read
+// costs a line per lane) the inputs are read once and the factors, which the
+// workspace holds in lane order, are read back instead: 32,768 lines of 1000
+// contiguous rows, FP64 shared operator, 0.68 ms keeping rows, 1.93 keeping
+// states; per-row 2.56 and 3.35 (stage_keeps_rows).
 //
 // Partition p of a system of n rows has m_p = floor(n/P) + (p < n mod P) rows
 // starting at p*floor(n/P) + min(p, n mod P).  Every system's arithmetic is
@@ -153,8 +160,7 @@ k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
         bad |= dev::bad_pivot(piv);
         st.step(ra, rc, rdd, dev::recip(piv));
     };
-    auto keep = [&](int g) {
-        const int64_t q = (int64_t)p * nseg + g;
+    auto keep = [&](int64_t q) {
         ws_d[q * nb + kl] = st.dh;
         if constexpr (SHARED_FACTORS) {
             if (kl == 0) {
@@ -167,7 +173,8 @@ k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
         }
     };
     // rows 2 .. m-1, a segment's loads in flight together
-    int j = 1, g = 0;
+    int j = 1;
+    int64_t g = (int64_t)p * nseg;
     for (; j + kSeg <= m - 1; j += kSeg, ++g) {
         T va[kSeg], vb[kSeg], vc[kSeg], vd[kSeg];
 #pragma unroll
@@ -192,6 +199,88 @@ k_stage_a(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
     red[red_at(3, p, kl, P, nb)] = (double)st.ah;
     red[red_at(4, p, kl, P, nb)] = (double)st.ch;
     red[red_at(5, p, kl, P, nb)] = (double)st.dh;
+    if (bad) atomicOr(err, 1);
+}
+
+// Stage A that keeps every interior row's d^, a^, c^: row r of batch-local
+// system k at r*nb + k (a^, c^ of a shared operator at r).
+template <typename T, bool LIKE_D, bool SHIFT>
+__global__ void __launch_bounds__(256)
+k_stage_a_rows(SysMap map, Coef coef, const T *__restrict__ d, T *__restrict__ ws_d,
+               T *__restrict__ ws_a, T *__restrict__ ws_c, double *__restrict__ red, int64_t k_begin,
+               int64_t nb, int P, int *err) {
+    constexpr bool SHARED_FACTORS = !LIKE_D && !SHIFT;
+    const int64_t kl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.y;
+    if (kl >= nb) return;
+    const dev::LaneSys sys = dev::lane_system(map, k_begin + kl);
+    const int64_t n = map.n;
+    const PartRange pr = part_range(n, P, p);
+    const T *__restrict__ A = (const T *)coef.a;
+    const T *__restrict__ B = (const T *)coef.b;
+    const T *__restrict__ C = (const T *)coef.c;
+    const int64_t rs = map.row_stride;
+    T sh = T(0);
+    if constexpr (SHIFT) sh = ((const T *)coef.shift)[sys.id];
+    auto load = [&](int64_t r, T &a, T &b, T &c, T &dd) {
+        const int64_t idx = sys.base + r * rs;
+        dd = d[idx];
+        if constexpr (LIKE_D) {
+            a = A[idx]; b = B[idx]; c = C[idx];
+        } else {
+            a = A[r]; b = B[r]; c = C[r];
+        }
+        if constexpr (SHIFT) b += sh;
+        if (r == 0) a = T(0);
+        if (r == n - 1) c = T(0);
+    };
+    // factor storage: row r of batch-local system kl at r*nb + kl (coalesced)
+    const bool store_factors = !SHARED_FACTORS || kl == 0;
+    const int64_t fk = SHARED_FACTORS ? 0 : kl;
+    const int64_t fstride = SHARED_FACTORS ? 1 : nb;
+    bool bad = false;
+    T a, b, c, dd;
+    load(pr.start, a, b, c, dd);
+    bad |= dev::bad_pivot(b);
+    T ib = dev::recip(b);
+    const T a0 = a * ib, c0 = c * ib, d0 = dd * ib;
+    load(pr.start + 1, a, b, c, dd);
+    bad |= dev::bad_pivot(b);
+    ib = dev::recip(b);
+    T ah = a * ib, ch = c * ib, dh = dd * ib;
+    T pi = T(1), dt1 = T(0), at1 = T(0);
+    const int m = pr.m;
+#pragma unroll 4
+    for (int j = 1; j < m - 1; ++j) {
+        // row j is final: store it, fold it into the row-1 spike, then advance
+        const int64_t r = pr.start + j;
+        ws_d[r * nb + kl] = dh;
+        if (store_factors) {
+            ws_a[r * fstride + fk] = ah;
+            ws_c[r * fstride + fk] = ch;
+        }
+        dt1 += pi * dh;
+        at1 += pi * ah;
+        pi = -ch * pi;
+        load(r + 1, a, b, c, dd);
+        const T piv = b - a * ch;
+        bad |= dev::bad_pivot(piv);
+        ib = dev::recip(piv);
+        const T ra = a * ib;
+        dh = (dd - a * dh) * ib;
+        ch = c * ib;
+        ah = -ra * ah;
+    }
+    const T ct1 = -pi;
+    const double den = 1.0 - (double)c0 * (double)at1;
+    bad |= dev::bad_pivot(den);
+    const double rho = dev::recip(den);
+    red[red_at(0, p, kl, P, nb)] = rho * (double)a0;
+    red[red_at(1, p, kl, P, nb)] = -rho * (double)c0 * (double)ct1;
+    red[red_at(2, p, kl, P, nb)] = rho * ((double)d0 - (double)c0 * (double)dt1);
+    red[red_at(3, p, kl, P, nb)] = (double)ah;
+    red[red_at(4, p, kl, P, nb)] = (double)ch;
+    red[red_at(5, p, kl, P, nb)] = (double)dh;
     if (bad) atomicOr(err, 1);
 }
 
@@ -270,6 +359,31 @@ k_stage_b_seq(const double *red, double *X, double *scratch, int64_t nb, int P, 
     if (bad) atomicOr(err, 1);
 }
 
+template <typename T, bool SHARED_FACTORS>
+__global__ void __launch_bounds__(256)
+k_stage_c_rows(SysMap map, T *__restrict__ x, const T *__restrict__ ws_d, const T *__restrict__ ws_a,
+               const T *__restrict__ ws_c, const double *__restrict__ X, int64_t k_begin, int64_t nb,
+               int P) {
+    const int64_t kl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = blockIdx.y;
+    if (kl >= nb) return;
+    const dev::LaneSys sys = dev::lane_system(map, k_begin + kl);
+    const PartRange pr = part_range(map.n, P, p);
+    const int64_t rs = map.row_stride;
+    const T xf = (T)X[(size_t)(2 * p) * nb + kl];
+    T xn = (T)X[(size_t)(2 * p + 1) * nb + kl];
+    const int64_t fk = SHARED_FACTORS ? 0 : kl;
+    const int64_t fstride = SHARED_FACTORS ? 1 : nb;
+    x[sys.base + (pr.start + pr.m - 1) * rs] = xn;
+#pragma unroll 4
+    for (int j = pr.m - 2; j >= 1; --j) {
+        const int64_t r = pr.start + j;
+        xn = ws_d[r * nb + kl] - ws_a[r * fstride + fk] * xf - ws_c[r * fstride + fk] * xn;
+        x[sys.base + r * rs] = xn;
+    }
+    x[sys.base + pr.start * rs] = xf;
+}
+
 // d and x may be the same array: no __restrict__ on either.
 template <typename T, bool LIKE_D, bool SHIFT>
 __global__ void __launch_bounds__(256)
@@ -342,9 +456,15 @@ hipError_t launch_a_t(const SysMap &map, const Coef &coef, const void *d, const 
                       int64_t nb, int P, int *err, hipStream_t st) {
     const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)P);
     const bool like_d = coef.mode == TDMA_COEF_LIKE_D, shift = coef.shift != nullptr;
-#define TDMA_A(LD, SH)                                                                          \
-    hipLaunchKernelGGL((k_stage_a<T, LD, SH>), grid, dim3(256), 0, st, map, coef, (const T *)d, \
-                       (T *)w.ws_d, (T *)w.ws_a, (T *)w.ws_c, w.red, k_begin, nb, P, w.nseg, err)
+#define TDMA_A(LD, SH)                                                                            \
+    if (w.keep_rows)                                                                              \
+        hipLaunchKernelGGL((k_stage_a_rows<T, LD, SH>), grid, dim3(256), 0, st, map, coef,       \
+                           (const T *)d, (T *)w.ws_d, (T *)w.ws_a, (T *)w.ws_c, w.red, k_begin,   \
+                           nb, P, err);                                                           \
+    else                                                                                          \
+        hipLaunchKernelGGL((k_stage_a<T, LD, SH>), grid, dim3(256), 0, st, map, coef,             \
+                           (const T *)d, (T *)w.ws_d, (T *)w.ws_a, (T *)w.ws_c, w.red, k_begin,   \
+                           nb, P, w.nseg, err)
     TDMA_STAGE_DISPATCH(TDMA_A)
 #undef TDMA_A
     return hipGetLastError();
@@ -355,6 +475,15 @@ hipError_t launch_c_t(const SysMap &map, const Coef &coef, const void *d, void *
                       int64_t k_begin, int64_t nb, int P, hipStream_t st) {
     const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)P);
     const bool like_d = coef.mode == TDMA_COEF_LIKE_D, shift = coef.shift != nullptr;
+    if (w.keep_rows) {
+        if (!like_d && !shift)
+            hipLaunchKernelGGL((k_stage_c_rows<T, true>), grid, dim3(256), 0, st, map, (T *)x,
+                               (const T *)w.ws_d, (const T *)w.ws_a, (const T *)w.ws_c, w.X, k_begin, nb, P);
+        else
+            hipLaunchKernelGGL((k_stage_c_rows<T, false>), grid, dim3(256), 0, st, map, (T *)x,
+                               (const T *)w.ws_d, (const T *)w.ws_a, (const T *)w.ws_c, w.X, k_begin, nb, P);
+        return hipGetLastError();
+    }
 #define TDMA_C(LD, SH)                                                                          \
     hipLaunchKernelGGL((k_stage_c<T, LD, SH>), grid, dim3(256), 0, st, map, coef, (const T *)d, \
                        (T *)x, (const T *)w.ws_d, (const T *)w.ws_a, (const T *)w.ws_c, w.X,    \
@@ -366,13 +495,28 @@ hipError_t launch_c_t(const SysMap &map, const Coef &coef, const void *d, void *
 
 }  // namespace
 
-size_t stage_ws(int dtype, const Coef &coef, int64_t n, int64_t batch, int P, void *mem, StageWs *out) {
+// Whether the staged solve keeps every row's factors: where fewer than 64 bytes of consecutive systems are adjacent (FP64, 32,768 lines of 1000
+// rows, shared operator, runs of 2 systems: 0.43 ms keeping rows, 0.79 keeping
+// states; FP32 runs of 4: 0.23 and 0.30, of 8: 0.16 and 0.15 per-row at 250 rows).
+// Also where partitions have fewer than kSeg / 2 interior rows, whose segment
+// reads and eliminates kSeg rows all the same (400,000 lines of 40 rows, 5 per
+// partition: 0.27 ms keeping rows, 0.33 keeping states).
+static bool stage_keeps_rows(const SysMap &map, size_t esz, int P) {
+    const int64_t stride = map.nsys0 > 1 ? map.sys_stride0 : map.sys_stride1;
+    const int64_t run = map.nsys0 > 1 ? map.nsys0 : map.nsys;
+    return stride != 1 || run * (int64_t)esz < 64 || map.n / P - 2 < kSeg / 2;
+}
+
+size_t stage_ws(int dtype, const SysMap &map, const Coef &coef, int64_t batch, int P, void *mem,
+                StageWs *out) {
     const size_t esz = dtype == TDMA_F64 ? 8 : 4;
+    const int64_t n = map.n;
     const auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const int64_t mmax = n / P + (n % P != 0);
     const int64_t nseg = mmax > 2 ? (mmax - 2 + kSeg - 1) / kSeg : 0;
     const bool shared_factors = coef.mode == TDMA_COEF_SHARED && coef.shift == nullptr;
-    const size_t states = (size_t)P * nseg;
+    out->keep_rows = stage_keeps_rows(map, esz, P);
+    const size_t states = out->keep_rows ? (size_t)n : (size_t)P * nseg;
     const size_t d_bytes = al(states * batch * esz);
     const size_t f_bytes = shared_factors ? al(states * esz) : d_bytes;
     const size_t red_bytes = al((size_t)6 * P * batch * 8), x_bytes = al((size_t)2 * P * batch * 8);

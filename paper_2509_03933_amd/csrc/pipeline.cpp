@@ -27,7 +27,6 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
     const Coef coef = make_coef(C);
     const int64_t nsys = map.nsys;
     if (nsys == 0) return TDMA_OK;
-    const int64_t n = L->n;
     batch = std::max<int64_t>(1, std::min(batch, nsys));
     const int64_t nbatches = (nsys + batch - 1) / batch;
     int nslots = schedule == 0 ? 3 : nstreams;
@@ -35,12 +34,12 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
 
     // per-slot workspace
     std::vector<StageWs> slots(nslots);
-    const size_t slot_bytes = stage_ws(dtype, coef, n, batch, P, nullptr, &slots[0]);
+    const size_t slot_bytes = stage_ws(dtype, map, coef, batch, P, nullptr, &slots[0]);
     void *ws = nullptr;
     int rc = ctx->workspace(1, slot_bytes * nslots, &ws);
     if (rc != TDMA_OK) return rc;
     for (int i = 0; i < nslots; ++i)
-        (void)stage_ws(dtype, coef, n, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
+        (void)stage_ws(dtype, map, coef, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
 
     // One batch has nothing to overlap with: its three stages run in sequence on
     // the library's first stream, with one fork and join.  Not on the caller's
