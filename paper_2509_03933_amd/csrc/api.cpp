@@ -746,16 +746,22 @@ int launch_ragged(const RaggedPlan &rp, const tdma_layout *L, const tdma_coeffs 
     return TDMA_OK;
 }
 
+// Kernels 3, 4 and 7 on systems of n rows: kernel 7 on partitions that cover n
+// exactly or (FP64) leave few of their slots empty.
+static bool shift_shape_ok(int dtype, int64_t n, const TileShape &sh) {
+    if (shift_supported(dtype, sh)) return sh.kernel != 7 || (int64_t)sh.P * sh.M == n || shift_uneven(n, sh);
+    if (dtype != TDMA_F64 || sh.P < 1 || !shift_uneven(n, sh)) return false;
+    TileShape widest = sh;
+    widest.M = 32;
+    return shift_supported(dtype, widest);
+}
+
 // Whether a tile shape can run a uniform layout with these coefficients.
-static bool shape_fits(int dtype, const tdma_layout *L, bool shared_op, const TileShape &sh,
-                       bool shifted_op, bool perrow_op) {
+bool shape_fits(int dtype, const tdma_layout *L, bool shared_op, const TileShape &sh,
+                bool shifted_op, bool perrow_op) {
     if ((int64_t)sh.P * sh.M < L->n) return false;
-    if (sh.kernel == 3 || sh.kernel == 4 || sh.kernel == 7) {
-        if (!shifted_op || !shift_supported(dtype, sh)) return false;
-        if (sh.kernel == 7 && (int64_t)sh.P * sh.M != L->n) return false;
-        const SysMap m = make_map(L);
-        return shift_layout_ok(m, sh);
-    }
+    if (sh.kernel == 3 || sh.kernel == 4 || sh.kernel == 7)
+        return shifted_op && shift_shape_ok(dtype, L->n, sh) && shift_layout_ok(make_map(L), sh);
     if (sh.kernel == 5) {
         if (!perrow_op || !perrow_supported(dtype, sh) || !perrow_layout_ok(make_map(L), sh)) return false;
         return sh.M == 16 || sh.M == 32 || perrow_uneven(L->n, sh);
@@ -766,13 +772,41 @@ static bool shape_fits(int dtype, const tdma_layout *L, bool shared_op, const Ti
     return !(sh.contig && fused_lds_bytes(dtype, sh) > 160 * 1024);
 }
 
+// The built-in rules (shared-operator kernel first where it applies); false: n is
+// too long for the fused path.
+bool builtin_shape(const tdma_layout *L, const tdma_coeffs *C, int dtype, TileShape *out) {
+    const int64_t nsys = L->nsys0 * L->nsys1;
+    const bool contig = L->row_stride == 1;
+    const bool shared_op = C->mode == TDMA_COEF_SHARED && C->b_shift == nullptr;
+    const bool shifted_op = C->mode == TDMA_COEF_SHARED && C->b_shift != nullptr;
+    const bool perrow_op = C->mode == TDMA_COEF_LIKE_D && C->b_shift == nullptr;
+    TileShape ssh;
+    if ((shared_op || (!contig && (shifted_op || perrow_op))) &&
+        small_shape(dtype, L->n, nsys, contig, perrow_op, shared_op, &ssh)) {
+        *out = ssh;
+        return true;
+    }
+    if ((shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
+         shift_layout_ok(make_map(L), ssh)) ||
+        (perrow_op && !contig && default_perrow_shape(dtype, L->n, nsys, &ssh) &&
+         perrow_layout_ok(make_map(L), ssh))) {
+        *out = ssh;
+        return true;
+    }
+    if (shared_op && default_shared_shape(dtype, L->n, nsys, contig, &ssh, true)) {
+        if (ssh.kernel == 6 && !shared_roll_ok(make_map(L), ssh))
+            default_shared_shape(dtype, L->n, nsys, contig, &ssh, false);
+        *out = ssh;
+        return true;
+    }
+    return default_shape(dtype, L->n, nsys, contig, C->mode == TDMA_COEF_LIKE_D, C->b_shift != nullptr, out);
+}
+
 // Tile shape of a uniform layout: the forced shape, else the autotune cache
 // (an entry that no longer fits, e.g. from an edited cache file, is
-// ignored), else the built-in rules (shared-operator kernel first where it
-// applies).
+// ignored), else the built-in rules.
 int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int dtype,
                  const TileShape *force, TileShape *out) {
-    const int64_t nsys = L->nsys0 * L->nsys1;
     TileShape sh;
     const bool contig = L->row_stride == 1;
     const bool shared_op = C->mode == TDMA_COEF_SHARED && C->b_shift == nullptr;
@@ -797,21 +831,7 @@ int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int
                         1 << sh.S_log2, sh.kernel);
     } else if (!(lookup_tuned(ctx->dev, L, C, dtype, &sh) && sh.contig == contig &&
                  shape_fits(dtype, L, shared_op, sh, shifted_op, perrow_op))) {
-        TileShape ssh;
-        if ((shared_op || (!contig && (shifted_op || perrow_op))) &&
-            small_shape(dtype, L->n, nsys, contig, perrow_op, shared_op, &ssh))
-            sh = ssh;
-        else if (shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
-            shift_layout_ok(make_map(L), ssh))
-            sh = ssh;
-        else if (perrow_op && !contig && default_perrow_shape(dtype, L->n, nsys, &ssh) &&
-                 perrow_layout_ok(make_map(L), ssh))
-            sh = ssh;
-        else if (shared_op && default_shared_shape(dtype, L->n, nsys, contig, &sh, true)) {
-            if (sh.kernel == 6 && !shared_roll_ok(make_map(L), sh))
-                default_shared_shape(dtype, L->n, nsys, contig, &sh, false);
-        } else if (!default_shape(dtype, L->n, nsys, contig, C->mode == TDMA_COEF_LIKE_D,
-                                  C->b_shift != nullptr, &sh))
+        if (!builtin_shape(L, C, dtype, &sh))
             return fail(TDMA_EUNSUPPORTED, "n = %lld is too long for the fused path (use "
                         "tdma_solve_partitioned)", (long long)L->n);
     }

@@ -86,6 +86,9 @@ constexpr int kRaggedAux = 3;
 int launch_ragged(const RaggedPlan &rp, const tdma_layout *L, const tdma_coeffs *C, int dtype,
                   const void *d, void *x, int *err, hipStream_t st, const hipStream_t *aux,
                   int naux, const hipEvent_t *ev);
+bool shape_fits(int dtype, const tdma_layout *L, bool shared_op, const TileShape &sh, bool shifted_op,
+                bool perrow_op);
+bool builtin_shape(const tdma_layout *L, const tdma_coeffs *C, int dtype, TileShape *out);
 int plan_uniform(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int dtype,
                  const TileShape *force, TileShape *out);
 int launch_uniform(const TileShape &sh, const tdma_layout *L, const tdma_coeffs *C, int dtype,

@@ -135,6 +135,10 @@ std::vector<TileShape> fused_candidates(int dtype, const tdma_layout *L, const t
     const int64_t n = L->n, nsys = L->nsys0 * L->nsys1;
     const bool contig = L->row_stride == 1;
     const bool shared_op = C->mode == TDMA_COEF_SHARED && C->b_shift == nullptr;
+    // the built-in rule's shape first: the winner is never slower than an
+    // untuned solve's
+    TileShape own;
+    if (builtin_shape(L, C, dtype, &own)) out.push_back(own);
     if (shared_op) {
         for (int M : {8, 12, 16, 24, 32}) {
             int P = 1;
@@ -158,20 +162,16 @@ std::vector<TileShape> fused_candidates(int dtype, const tdma_layout *L, const t
     const bool shifted_op = C->mode == TDMA_COEF_SHARED && C->b_shift != nullptr;
     const bool perrow_op = C->mode == TDMA_COEF_LIKE_D && C->b_shift == nullptr;
     if (!contig && (shifted_op || perrow_op)) {
-        const SysMap m = make_map(L);
-        for (int M : {8, 16, 32}) {
+        for (int M : {8, 16, 20, 24, 28, 32}) {
             int P = 2;
             while ((int64_t)P * M < n) P <<= 1;
             if (P > 64) continue;
-            for (int S_log2 = 2; S_log2 <= 5; ++S_log2) {
+            for (int S_log2 = 2; S_log2 <= (perrow_op ? 7 : 5); ++S_log2) {
                 for (int kind : {3, 4, 5, 7}) {
                     if ((kind == 5) != perrow_op) continue;
-                    if (kind == 7 && (int64_t)P * M != n) continue;
                     TileShape sh;
                     sh.kernel = kind; sh.M = M; sh.P = P; sh.S_log2 = S_log2; sh.contig = false;
-                    const bool ok = kind == 5 ? perrow_supported(dtype, sh) && perrow_layout_ok(m, sh)
-                                              : shift_supported(dtype, sh) && shift_layout_ok(m, sh);
-                    if (ok) out.push_back(sh);
+                    if (shape_fits(dtype, L, false, sh, shifted_op, perrow_op)) out.push_back(sh);
                 }
             }
         }
