@@ -194,11 +194,13 @@ static int ilog2_floor(int64_t v) {
 
 // Contiguous per-row lines: systems per block (up to 192 lanes) such that the
 // fewest lanes of its wavefronts idle, the smaller block on ties (one
-// wavefront where that loses nothing: its barriers cost nothing).
+// wavefront where that loses nothing: its barriers cost nothing).  Lines of one
+// partition take 64 systems (FP32, 2^26 unknowns in lines of 8 rows: 242 us, with 32
+// 410).
 static int contig_perrow_s_log2(int64_t P) {
     int best = 0;
     double best_use = 0.0;
-    for (int s = 0; s <= 5; ++s) {
+    for (int s = 0; s <= 6; ++s) {
         const int64_t lanes = P << s;
         if (lanes > 192 && s > 0) break;
         const double use = (double)lanes / (double)((lanes + 63) / 64 * 64);
@@ -344,8 +346,11 @@ static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool li
 // below 8 (300,000 x 96: 12 x 8 partitions 92 us, 24 x 4 101).  Strided layouts take
 // S = 32 systems per tile (measured best on the 256^3 ADI sweep in FP64 and
 // FP32), contiguous rows S = 16 and at least 256 lanes (FP64 at 16 rows and
-// 16 partitions or more: S = 8, where two blocks fit a CU's LDS), at most 32;
-// both as far as the lanes and LDS allow.  Contiguous x-lines of n = 768 (FP64): 24 rows x 32
+// 16 partitions or more: S = 8, where two blocks fit a CU's LDS; FP64 at most 32,
+// one partition of more than 16 rows 64); both as far as the lanes and LDS
+// allow.  Lines of one short partition want the whole block: 33.5 M lines of 2
+// rows (FP64) 412 us with 256 systems, 635 with 32, FP32 20 rows 128 with 256, 208
+// with 32; but FP64 31 rows 440 with 256, 310 with 64.  Contiguous x-lines of n = 768 (FP64): 24 rows x 32
 // partitions x 16 systems 1.94 ms, 12 x 64 x 8 2.26 ms, 24 x 32 x 8 2.68 ms;
 // n = 384: 24 x 16 x 16 0.248 ms, 12 x 32 x 8 0.279 ms; 167,680 x 200: 16 x 16 x 8
 // 0.118, 16 x 16 x 16 0.130; 480,000 x 250: 0.393, 0.383, 32 x 8 x 32 0.495; 100,000 x 512: 16 x 32 x 8 0.182, 16 x 32 x 16
@@ -368,7 +373,8 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
         sh.M = M;
         sh.P = (int)P;
         sh.contig = contig;
-        int64_t S_want = contig ? std::min<int64_t>(32, std::max<int64_t>(16, 256 / P)) : 32;
+        int64_t S_want = contig ? std::max<int64_t>(16, 256 / P) : 32;
+        if (contig && dtype == TDMA_F64 && (P > 1 || M > 16)) S_want = std::min<int64_t>(S_want, P > 1 ? 32 : 64);
         if (contig && dtype == TDMA_F64 && M == 16 && P >= 16) S_want = 8;
         int S_log2 = ilog2_floor(S_want);
         const int maxt = shared_max_threads(dtype, M, sh.kernel, contig);
