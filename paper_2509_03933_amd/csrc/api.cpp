@@ -219,7 +219,8 @@ static int contig_perrow_s_log2(int64_t P) {
 // Small problems (fewer than 2^20 unknowns; contiguous per-row FP64 lines
 // 2^19) are latency-bound: short partitions (M = 4 first) and one system per
 // tile, so the solve spreads over as many CUs as it can and each lane's
-// serial chain is short.
+// serial chain is short.  (A block has 16 lanes at least: shifted x-lines of 2
+// rows, 2^19 unknowns, blocks of one lane 60 us, of 16 16.)
 // Contiguous per-row FP64 lines beyond that: 8 rows per lane up to 2,048
 // rows.  A lane holds all four inputs of its rows, so 8 rows take half the
 // registers of 16 and twice the blocks run per CU, one's loads beside the
@@ -261,7 +262,10 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
         while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
         // a tile larger than the number of systems only wastes lanes
         while (S_log2 > 0 && ((int64_t)1 << (S_log2 - 1)) >= nsys) --S_log2;
-        if (small) S_log2 = 0;
+        if (small) {
+            S_log2 = 0;
+            while (P << S_log2 < 16) ++S_log2;
+        }
         sh.S_log2 = S_log2;
         if (((int64_t)1 << S_log2) * P > maxt) continue;
         if (contig && fused_lds_bytes(dtype, sh) > 96 * 1024) continue;
@@ -271,15 +275,18 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
     return false;
 }
 
+bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileShape *out, bool allow_roll);
+
 // Batches too small to give every CU a tile or two of the walking kernels
 // (shared operator; strided rows also with a shift or per-row coefficients):
 // the generic kernel with small blocks.  The walking kernels' long unrolled
 // bodies and per-block tables pay over many tiles; on a few, each block runs
 // its code once, cold, and most CUs have none.  16 rows per lane for strided
-// rows (the partition length of the kernels it stands in for, so the
-// interface system and its rounding stay the same), 8 for contiguous ones;
-// blocks of 128 lanes below 2^19 unknowns, 256 (contiguous 512) above.  The
-// block has its lanes whatever the system count: those past the last system
+// rows (the walking kernels have 8 to 32), 8 for contiguous ones;
+// blocks of 128 lanes below 2^19 unknowns, 256 (contiguous 512) above, and
+// most of a wavefront at least: short lines take up to 64 systems per block
+// (500,000 unknowns in z-lines of 2 rows, FP32 per-row: 118 us in blocks of one
+// lane, 7.5 in blocks of 64; walking 36).  The block has its lanes whatever the system count: those past the last system
 // load operator rows too.  Walking against generic kernel, us per call in a
 // captured stream, FP64, lines of n rows x systems: shared z-lines 128 x 64
 // 9.7 / 5.1, 1000 x 64 23.1 / 8.7, 1000 x 1024 22.7 / 11.1, 1000 x 2500 28.5 /
@@ -287,18 +294,53 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
 // 1024 20.7 / 11.2, 1000 x 2500 27.8 / 19.1, 1000 x 4096 25.4 / 26.9; shared
 // x-lines 250 x 256 18.2 / 8.3, 1000 x 1024 21.1 / 13.7, 777 x 2500 28.9 / 29.0;
 // per-row z-lines 250 x 256 15.6 / 6.1, 1000 x 1024 34.7 / 14.6, 512 x 4096
-// 17.1 / 19.0.  Hence the lines at 3 x 2^20 unknowns, and at 3 x 2^19 for
-// contiguous rows and per-row coefficients.  FP32 per-row lines of up to 128
-// rows stay with the walking kernel (4.5 against 5.1 us).  FP32 batches of a
+// 17.1 / 19.0.  small_limit draws the line from these.  Contiguous lines that no
+// streaming shape holds keep default_shape's tiles, those of fewer than 16 rows
+// the streaming kernel (2 rows, 262,144 unknowns: 8.3 / 9.6).  FP32 per-row lines
+// of 28 to 128 rows stay with the walking kernel (4.5 against 5.1 us), and so do
+// fewer than 16 per-row lines that fill 32 or 64 partitions of 32 rows (8 x 1024,
+// FP32, 7.4 against 9.1).  FP32 batches of a
 // shared operator keep the shared-operator kernel, whose factors are formed in
 // FP64, with small tiles of short partitions (one tile per block on strided
 // rows): z-lines 250 x 64 11.6 -> 8.0 us, 1000 x 1024 16.9 -> 13.2, x-lines 250 x
 // 64 17.3 -> 8.6, 1000 x 1024 25.1 -> 12.9.
+//
+// small_limit: the unknowns from which the walking kernels (past 2,048 rows
+// default_shape's wider tiles) are the faster ones: 3 x 2^20, and 3 x 2^19 for
+// contiguous rows and per-row coefficients.  Earlier where the generic kernel's
+// blocks hold few systems or the walking tiles are the best filled, walking
+// against generic kernel: shared lines of up to 48 rows 2^20 (40 rows, 2^21.4
+// unknowns: 15.0 / 16.9), of more than 1,024 rows 2^21 (2000 rows in y, 2^21.3: 27.6 /
+// 38.6; 2^20.9: 27.1 / 24.7), shifted FP64 ones 2^20 (2000 rows in y, 2^21.2: 21.6 /
+// 39.5) and 2^21 where they fill 64 partitions (2048 rows, 2^20.8: 35.3 / 25.8), per-row
+// lines of 512 rows, which fill 16 partitions, 2^20 (in y, 2^20.2: 15.2 / 24.4).
+// FP32 shared ones against their small tiles: 2^20 up to 256 rows, 3 x 2^19 where the
+// streaming kernel has 12 or 24 rows per lane (640 rows, 2^21.4: 17 / 27; 512 rows
+// 13.6 / 11.4).  Past 2,048 rows 2^20 for per-row lines and shifted FP32 ones (4096
+// rows, 2^19.3: 29 / 24; 2500 rows, 2^20.3: 27 / 46), none for the others (614 FP64
+// lines of 4096 rows: 37 / 50).
+static int64_t small_limit(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shared_op) {
+    const int64_t k19 = (int64_t)1 << 19;
+    if (contig) return 3 * k19;
+    if (n > 2048) return like_d || (dtype == TDMA_F32 && !shared_op) ? 2 * k19 : 0;
+    if (like_d) return n == 16 * 32 ? 2 * k19 : 3 * k19;
+    if (shared_op) {
+        if (n <= 48 || (dtype == TDMA_F32 && n <= 256)) return 2 * k19;
+        TileShape w;
+        if (dtype == TDMA_F32 && default_shared_shape(dtype, n, nsys, false, &w, true) && (w.M == 12 || w.M == 24))
+            return 3 * k19;
+    }
+    if (n > 1024 && dtype == TDMA_F64) return shared_op || n == 64 * 32 ? 4 * k19 : 2 * k19;
+    return 6 * k19;
+}
+
 static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shared_op,
                         TileShape *out) {
-    if (n > 16384 || (like_d && dtype == TDMA_F32 && n <= 128)) return false;
+    if (n > 16384 || (contig && n < 16)) return false;
+    if (like_d && dtype == TDMA_F32 && n >= 28 && n <= 128) return false;
+    if (like_d && nsys < 16 && (n == 32 * 32 || n == 64 * 32)) return false;
     const int64_t total = n * nsys;
-    if (total >= (int64_t)3 << (contig || like_d ? 19 : 20)) return false;
+    if (total >= small_limit(dtype, n, nsys, contig, like_d, shared_op)) return false;
     if (shared_op && dtype == TDMA_F32) {
         TileShape sh;
         sh.kernel = contig ? 2 : 1;
@@ -310,6 +352,7 @@ static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool li
         const int lanes = total >= ((int64_t)1 << 19) ? 512 : (sh.P > 32 ? 256 : 128);
         sh.S_log2 = 4;
         while (sh.S_log2 > 0 && sh.P << sh.S_log2 > lanes) --sh.S_log2;
+        while (sh.P << sh.S_log2 < 48) ++sh.S_log2;
         if (!shared_supported(dtype, sh)) return false;
         *out = sh;
         return true;
@@ -326,6 +369,9 @@ static bool small_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool li
         sh.contig = contig;
         sh.S_log2 = 4;
         while (sh.S_log2 > 0 && P << sh.S_log2 > lanes) --sh.S_log2;
+        while (P << sh.S_log2 < 48) ++sh.S_log2;
+        // (per-row lines have no operator rows to load: no lanes past the last system)
+        while (like_d && sh.S_log2 > 0 && ((int64_t)1 << (sh.S_log2 - 1)) >= nsys) --sh.S_log2;
         if (!fused_supported(dtype, sh) || (contig && fused_lds_bytes(dtype, sh) > 96 * 1024)) continue;
         *out = sh;
         return true;
@@ -787,7 +833,8 @@ bool builtin_shape(const tdma_layout *L, const tdma_coeffs *C, int dtype, TileSh
     const bool shifted_op = C->mode == TDMA_COEF_SHARED && C->b_shift != nullptr;
     const bool perrow_op = C->mode == TDMA_COEF_LIKE_D && C->b_shift == nullptr;
     TileShape ssh;
-    if ((shared_op || (!contig && (shifted_op || perrow_op))) &&
+    if ((contig ? shared_op && default_shared_shape(dtype, L->n, nsys, true, &ssh, true)
+                : shared_op || shifted_op || perrow_op) &&
         small_shape(dtype, L->n, nsys, contig, perrow_op, shared_op, &ssh)) {
         *out = ssh;
         return true;

@@ -27,11 +27,18 @@ def _layout(axis, n, nsys):
 
 
 # (kind, dtype, axis, n, systems)
+SMALL = [(kind, dt, axis, n, nsys)
+         for kind in ("shared", "shift", "perrow") for dt in ("f64", "f32") for axis in ("x", "z")
+         for n, nsys in ((2, 1), (2, 129), (3, 40001), (8, 65), (15, 700), (16, 1000), (17, 65), (27, 130),
+                         (40, 33), (48, 4097), (49, 31), (130, 5), (600, 9))]
+SMALL += [(kind, dt, "z", n, nsys)
+          for kind in ("shared", "shift", "perrow") for dt in ("f64", "f32")
+          for n, nsys in ((2048, 17), (2049, 17), (1024, 15), (1025, 1100), (512, 2049), (40, 27001))]
 CONTIG = [(kind, dt, "x", n, nsys)
           for kind in ("shared", "perrow") for dt in ("f64", "f32")
           for n, nsys in ((2, 300), (8, 257), (9, 1000), (14, 513), (20, 80001), (24, 65537), (31, 51001), (16, 98305),
                           (6, 174801), (40, 39401))]
-CASES = CONTIG
+CASES = SMALL + CONTIG
 
 
 @pytest.mark.parametrize("kind,dt,axis,n,nsys", CASES)

@@ -37,3 +37,42 @@ def test_short_contiguous_lines_fill_a_wavefront(kind, dt, lg):
     for n in range(2, 33):
         kernel, M, P, S = _builtin(kind, dt, "x", n, (1 << lg) // n)
         assert P * S >= 60, (n, kernel, M, P, S)
+
+@pytest.mark.parametrize("kind", ["shared", "shift", "perrow"])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("axis", ["x", "z"])
+def test_small_batches_of_short_lines_share_blocks(kind, dt, axis):
+    """No block of a lane or two where systems enough are there to share one."""
+    for lg in (13, 16, 18, 19, 20, 21):
+        for n in list(range(2, 34)) + [40, 48, 49, 64, 100]:
+            nsys = (1 << lg) // n
+            kernel, M, P, S = _builtin(kind, dt, axis, n, nsys)
+            assert P * S >= 16, (n, nsys, kernel, M, P, S)
+            if axis == "z" and kernel in (0, 1):      # one tile per block
+                assert P * S >= 48 or S >= nsys, (n, nsys, kernel, M, P, S)
+
+
+@pytest.mark.parametrize("dt,kind,axis,n,nsys,run,walking", [
+    ("f64", "shared", "z", 40, (1 << 21) // 40, None, True),
+    ("f64", "shared", "z", 40, (1 << 19) // 40, None, False),
+    ("f64", "shared", "y", 2000, 1536, 256, True),
+    ("f64", "shared", "y", 2000, 768, 256, False),
+    ("f32", "shared", "z", 640, (1 << 21) // 640, None, True),
+    ("f64", "shift", "y", 2000, 1024, 256, True),
+    ("f64", "shift", "y", 2000, 256, 256, False),
+    ("f64", "perrow", "y", 512, 2304, 256, True),
+    ("f64", "perrow", "y", 512, 1536, 256, False),
+    ("f32", "perrow", "z", 1024, 8, None, True),
+    ("f64", "shared", "x", 8, 30000, None, True),
+    ("f64", "shared", "x", 16, 30000, None, False)])
+def test_small_rule_gives_way_to_the_walking_kernels(dt, kind, axis, n, nsys, run, walking):
+    kernel, M, P, S = _builtin(kind, dt, axis, n, nsys, run)
+    small = kernel == 0 or (kind == "shared" and dt == "f32" and kernel == 1)
+    assert small != walking, (kernel, M, P, S)
+
+
+@pytest.mark.parametrize("kind", ["shared", "shift"])
+def test_lines_past_the_walking_kernels_keep_wide_tiles(kind):
+    for n in (2500, 4096):
+        for lg in (20.2, 20.9, 21.4):
+            assert _builtin(kind, "f64", "z", n, int(2 ** lg / n))[3] > 1, (n, lg)
