@@ -216,8 +216,8 @@ static int contig_perrow_s_log2(int64_t P) {
 // Strided systems: S consecutive systems per tile so that each row load is a
 // full 128-byte line (S = 16 in FP64, 32 in FP32); P partitions of M rows so
 // that P*M covers n.  Contiguous rows: the tile is staged through LDS.
-// Small problems (fewer than 2^20 unknowns; contiguous per-row FP64 lines
-// 2^19) are latency-bound: short partitions (M = 4 first) and one system per
+// Small problems (fewer than 2^20 unknowns; contiguous FP64 lines that take 8
+// rows per lane 2^19) are latency-bound: short partitions (M = 4 first) and one system per
 // tile, so the solve spreads over as many CUs as it can and each lane's
 // serial chain is short.  (A block has 16 lanes at least: shifted x-lines of 2
 // rows, 2^19 unknowns, blocks of one lane 60 us, of 16 16.)
@@ -232,13 +232,14 @@ static int contig_perrow_s_log2(int64_t P) {
 // us, S = 2 149; 27,904 x 600: S = 2, 150 lanes, 157, S = 1 176).
 // Contiguous lines of a shared operator past the streaming kernel's lengths:
 // 8 rows per lane in FP64 and about 512 lanes (16,384 x 2048 315 -> 256 us,
-// 11,136 x 3000 529 -> 365; FP32, 16 rows, 11,136 x 3000 331 -> 220).
+// 11,136 x 3000 529 -> 365; FP32, 16 rows, 11,136 x 3000 331 -> 220), fewer where
+// that leaves less than half a block per CU (FP32, 215 x 6000: S = 1 26 us, 2 34).
 bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shift,
                    TileShape *out) {
     const int esz = dtype == TDMA_F64 ? 8 : 4;
     const bool lines = contig && like_d, long_shared = contig && !like_d && !shift;
     const bool rows8 = dtype == TDMA_F64 && ((lines && n <= 2048) || long_shared);
-    const bool small = n * nsys < ((int64_t)1 << (lines && rows8 ? 19 : 20));
+    const bool small = n * nsys < ((int64_t)1 << (rows8 ? 19 : 20));
     const int Ms_rows8[] = {8, 16, 4};
     const int Ms_f64[] = {16, 8, 4};
     const int Ms_f32[] = {16, 32, 8, 4};
@@ -257,7 +258,10 @@ bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d,
         // short strided lines: a wavefront's worth of lanes (n = 4: 1283 -> 557 us)
         while (!contig && S_log2 < 6 && P << S_log2 < 64) ++S_log2;
         if (lines) S_log2 = contig_perrow_s_log2(P);
-        if (long_shared) S_log2 = ilog2_floor(std::max<int64_t>(1, std::min<int64_t>(16 / esz, 768 / P)));
+        if (long_shared) {
+            S_log2 = ilog2_floor(std::max<int64_t>(1, std::min<int64_t>(16 / esz, 768 / P)));
+            while (S_log2 > 0 && nsys < ((int64_t)128 << S_log2)) --S_log2;
+        }
         const int maxt = fused_max_threads(dtype, M);
         while (S_log2 > 0 && ((int64_t)1 << S_log2) * P > maxt) --S_log2;
         // a tile larger than the number of systems only wastes lanes

@@ -38,7 +38,9 @@ CONTIG = [(kind, dt, "x", n, nsys)
           for kind in ("shared", "perrow") for dt in ("f64", "f32")
           for n, nsys in ((2, 300), (8, 257), (9, 1000), (14, 513), (20, 80001), (24, 65537), (31, 51001), (16, 98305),
                           (6, 174801), (40, 39401))]
-CASES = SMALL + CONTIG
+LONG = [("shared", dt, "x", n, nsys) for dt in ("f64", "f32")
+        for n, nsys in ((2000, 265), (2100, 255), (3000, 511), (3000, 513), (6000, 215), (6000, 257))]
+CASES = SMALL + CONTIG + LONG
 
 
 @pytest.mark.parametrize("kind,dt,axis,n,nsys", CASES)

@@ -76,3 +76,13 @@ def test_lines_past_the_walking_kernels_keep_wide_tiles(kind):
     for n in (2500, 4096):
         for lg in (20.2, 20.9, 21.4):
             assert _builtin(kind, "f64", "z", n, int(2 ** lg / n))[3] > 1, (n, lg)
+
+@pytest.mark.parametrize("n,nsys,dt,S", [(6000, 215, "f32", 1), (6000, 700, "f32", 2), (3000, 925, "f32", 4),
+                                         (3000, 10000, "f64", 2), (2500, 250, "f64", 1)])
+def test_few_long_contiguous_lines_take_a_block_each(n, nsys, dt, S):
+    assert _builtin("shared", dt, "x", n, nsys)[3] == S
+
+
+def test_contiguous_shared_lines_of_8_rows_per_lane_from_2_19():
+    assert _builtin("shared", "f64", "x", 2000, 400)[1] == 8
+    assert _builtin("shared", "f64", "x", 2000, 100)[1] == 4
