@@ -466,7 +466,12 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
 // FFT-Poisson lines).  FP64 above 256 rows: the walk that recomputes its pivots
 // (kernel 7), P the fewest partitions (16, 32 or 64) of at most 32 rows, the
 // rows spread evenly over them in M = 20, 24, 28 or 32 slots, and S = 32
-// consecutive systems (256-byte rows; 16 with 64 partitions).  Up to 256 rows:
+// consecutive systems (256-byte rows; 16 with 64 partitions).  Above 896 rows,
+// where the tiles are few (2.5 per CU; 0.75 where the slots stay a quarter empty in
+// kernel 3) and the rows lie less than 32 KB apart: kernel 3, whose shorter chain
+// per tile and half as wide tiles fill the chip sooner (y-lines of 256 systems,
+// 2^22 unknowns, 2000 rows: 22.5 against 38; 2^24.5: 0.87 of kernel 3's time in
+// kernel 7; z-lines of 1000 rows, 2^22.3: kernel 7 0.78).  Up to 256 rows:
 // lengths that fill partitions of 32 rows take the rolling walk that keeps
 // its pivots (kernel 3) with S = 32, others the generic kernel (false).  FP32:
 // kernel 3, M = 32 rows per lane (else 16, 8), P a power of two <= 64, S = 32.
@@ -476,7 +481,7 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
 // 665 and 1043; n = 64 kernel 3
 // 453 (S = 16 498, kernel 7 472), 256 458 (538, 494); n = 40 generic 498, kernel
 // 3 with identity rows 1158, 100 464 and 624, 200 488 and 647.
-static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, TileShape *out) {
+static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, int64_t row_stride, TileShape *out) {
     TileShape sh;
     sh.contig = false;
     if (dtype == TDMA_F64) {
@@ -493,6 +498,13 @@ static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, TileShape *o
             sh.M = (int)(((n + P - 1) / P + 3) / 4 * 4);
         }
         sh.S_log2 = P > 32 ? 4 : 5;
+        const int64_t tiles_min = 4 * n < 3 * 32 * P ? 192 : 640;
+        if (sh.kernel == 7 && n > 896 && (P > 32 || n < 32 * P) && row_stride < 4096 &&
+            nsys < tiles_min << sh.S_log2) {
+            sh.kernel = 3;
+            sh.M = 32;
+            --sh.S_log2;
+        }
         while (sh.S_log2 > 0 && ((int64_t)1 << (sh.S_log2 - 1)) >= nsys) --sh.S_log2;
         if (!shift_uneven(n, sh) && !shift_supported(dtype, sh)) return false;
         *out = sh;
@@ -843,7 +855,7 @@ bool builtin_shape(const tdma_layout *L, const tdma_coeffs *C, int dtype, TileSh
         *out = ssh;
         return true;
     }
-    if ((shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, &ssh) &&
+    if ((shifted_op && !contig && default_shift_shape(dtype, L->n, nsys, L->row_stride, &ssh) &&
          shift_layout_ok(make_map(L), ssh)) ||
         (perrow_op && !contig && default_perrow_shape(dtype, L->n, nsys, &ssh) &&
          perrow_layout_ok(make_map(L), ssh))) {

@@ -86,3 +86,11 @@ def test_few_long_contiguous_lines_take_a_block_each(n, nsys, dt, S):
 def test_contiguous_shared_lines_of_8_rows_per_lane_from_2_19():
     assert _builtin("shared", "f64", "x", 2000, 400)[1] == 8
     assert _builtin("shared", "f64", "x", 2000, 100)[1] == 4
+
+@pytest.mark.parametrize("n,nsys,run,kernel", [
+    (1000, 1 << 12, 256, 3), (1000, 1 << 13, 256, 3), (1000, 1 << 15, 256, 7), (2000, 1 << 12, 256, 3),
+    (2000, 1 << 14, 256, 7), (2048, 1 << 12, 256, 3), (1300, 1 << 11, 256, 3), (1300, 1 << 12, 256, 7),
+    (700, 1 << 13, 256, 7), (1024, 1 << 12, 256, 7), (1000, 1 << 13, 1 << 13, 7)])
+def test_few_tiles_of_long_shifted_lines_take_kernel_3(n, nsys, run, kernel):
+    """Kernel 7 needs tiles enough, or rows far apart (the last case)."""
+    assert _builtin("shift", "f64", "y", n, nsys, run)[0] == kernel
