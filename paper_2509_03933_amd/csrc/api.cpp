@@ -533,7 +533,11 @@ static bool default_shift_shape(int dtype, int64_t n, int64_t nsys, int64_t row_
 // them; M the slots that hold ceil(n/P) rows (16, 20, 24, 28 or 32).  S
 // systems so that a tile fills 512 lanes (FP32 1024 from 16 partitions on,
 // 512 there for M above 24 unless n fills it), halved to no less than a
-// 128-byte tile row while the tiles are fewer than two per CU.  Measured on
+// 128-byte tile row while the tiles are fewer than two per CU (FP32 to 64 bytes,
+// 32 with 64 partitions, while they are fewer than 128: 2048 rows, 2^20.7
+// unknowns in y, 8 systems 24 us, 16 37; 1024 rows, 2^21, 16 systems 27, 32 33).
+// FP32 lines of 64 and 128 rows below 2^19 unknowns take 16 rows per lane (64 x
+// 1024 5.7 us, 32 rows 7.1).  Measured on
 // 2^26 unknowns in lines along z, us, against the best of 16 and 32 rows per
 // lane with identity rows past the end and 64- or 128-byte tile rows: FP64 n =
 // 100 490, 16 x 8 x 32 545; 500 558, 730; 512 555, 643; 768 603, 914; 1000 640,
@@ -548,6 +552,8 @@ static bool default_perrow_shape(int dtype, int64_t n, int64_t nsys, TileShape *
     if (P > 64) return false;
     TileShape sh;
     sh.kernel = 5;
+    // FP32 below 2^19 unknowns: 16 rows where they fill exactly
+    if (dtype == TDMA_F32 && n <= 128 && n == 32 * P && n * nsys < ((int64_t)1 << 19)) P *= 2;
     sh.M = (int)std::max<int64_t>(16, ((n + P - 1) / P + 3) / 4 * 4);
     sh.P = (int)P;
     sh.contig = false;
@@ -557,6 +563,7 @@ static bool default_perrow_shape(int dtype, int64_t n, int64_t nsys, TileShape *
     const int64_t S_min = 128 / (dtype == TDMA_F64 ? 8 : 4);
     int64_t S = std::min<int64_t>(128, (wide ? 1024 : 512) / P);
     while (S > S_min && nsys < S * 512) S >>= 1;
+    while (dtype == TDMA_F32 && S > (P > 32 ? 8 : 16) && nsys < S * 128) S >>= 1;
     while (S > 1 && S / 2 >= nsys) S >>= 1;
     sh.S_log2 = ilog2_floor(S);
     if (!perrow_supported(dtype, sh)) return false;

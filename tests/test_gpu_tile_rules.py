@@ -42,7 +42,9 @@ LONG = [("shared", dt, "x", n, nsys) for dt in ("f64", "f32")
         for n, nsys in ((2000, 265), (2100, 255), (3000, 511), (3000, 513), (6000, 215), (6000, 257))]
 SHIFTED = [("shift", "f64", axis, n, nsys) for axis in ("y", "z")
            for n, nsys in ((897, 3600), (1000, 3201), (1000, 5001), (1300, 2500), (1900, 1105), (2048, 1100))]
-CASES = SMALL + CONTIG + LONG + SHIFTED
+PERROW32 = [("perrow", "f32", axis, n, nsys) for axis in ("y", "z")
+            for n, nsys in ((64, 1000), (128, 31), (64, 8300), (1000, 1700), (1024, 4001), (2048, 1009))]
+CASES = SMALL + CONTIG + LONG + SHIFTED + PERROW32
 
 
 @pytest.mark.parametrize("kind,dt,axis,n,nsys", CASES)
