@@ -95,7 +95,7 @@ def test_few_tiles_of_long_shifted_lines_take_kernel_3(n, nsys, run, kernel):
     """Kernel 7 needs tiles enough, or rows far apart (the last case)."""
     assert _builtin("shift", "f64", "y", n, nsys, run)[0] == kernel
 
-@pytest.mark.parametrize("n,nsys,M,P,S", [(64, 1000, 16, 4, 32), (128, 1000, 16, 8, 32), (64, 100000, 32, 2, 128),
+@pytest.mark.parametrize("n,nsys,M,P,S", [(64, 1000, 16, 4, 16), (128, 1000, 16, 8, 16), (64, 100000, 32, 2, 128),
                                           (1024, 2000, 32, 32, 16), (1024, 5000, 32, 32, 32), (2048, 900, 32, 64, 8),
                                           (2048, 2100, 32, 64, 16)])
 def test_fp32_per_row_lines_of_few_tiles(n, nsys, M, P, S):
