@@ -155,9 +155,13 @@ static int refined_run(const tdma_layout *layout, const tdma_coeffs *coeffs, con
         e = launch_refine(map, coef, sh, d, x, c.iters, c.tol, state, st);
     if (e != hipSuccess) return hip_fail(e, "refine launch");
     if (c.fallback) {
+        // blocks of 256 lanes whatever the coefficients (default_shape's rule
+        // for shifted lines): the grid covers `capacity` systems and nearly
+        // all of its blocks only find their place past the count, so few large
+        // ones are the quickest (contiguous shared lines of 64 rows, 65,536 of
+        // them: the call 50 us, with the 64-lane blocks of a solve 57)
         TileShape fsh;
-        if (!default_shape(TDMA_F64, layout->n, capacity, layout->row_stride == 1,
-                           coeffs->mode == TDMA_COEF_LIKE_D, coeffs->b_shift != nullptr, &fsh))
+        if (!default_shape(TDMA_F64, layout->n, capacity, layout->row_stride == 1, false, true, &fsh))
             return fail(TDMA_EUNSUPPORTED, "no FP64 fallback tile for n = %lld", (long long)layout->n);
         SysMap fm = map;
         fm.nsys = capacity;
