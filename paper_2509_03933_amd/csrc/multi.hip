@@ -230,11 +230,13 @@ inline size_t multi_lds_bytes(size_t esz, int S, int P, int M, int NR) {
 // the same memory channels, scattered ones do not.  With spread == 0 the
 // order is XCD-aware (dev::xcd_tile), for tile rows narrower than a line.
 // x may alias d: a block reads all of its tile before it writes any of it.
-// pin (x not d): system 0 has an operator of its own, the tables a, b, c of n
+// PIN (x not d): system 0 has an operator of its own, the tables a, b, c of n
 // rows at pin, without a shift; one block more than the tiles solves it, and
 // the block whose tile holds system 0 leaves it out (a launch of its own for
-// that one system took 12 us of a small FFT-Poisson step's 40).
-template <typename T, int M, int NR, bool SHIFT, bool VEC>
+// that one system took 12 us of a small FFT-Poisson step's 40).  An instance of
+// its own: asked at run time, pin cost the other callers 1 to 17% (32,768 FP32
+// lines of 16 rows: 12.8 us, 15.0).
+template <typename T, int M, int NR, bool SHIFT, bool VEC, bool PIN>
 __global__ void __launch_bounds__(512)
 k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2, int P_log2,
         int64_t spread, const T *pin, int *err) {
@@ -247,8 +249,8 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
     const int p = tid >> S_log2;
     const int r0 = p * M;
     const int R = P * M;
-    const int64_t nb = (int64_t)gridDim.x - (pin ? 1 : 0);
-    const bool pinned = pin && (int64_t)blockIdx.x == nb;
+    const int64_t nb = (int64_t)gridDim.x - (PIN ? 1 : 0);
+    const bool pinned = PIN && (int64_t)blockIdx.x == nb;
     const int64_t k0 = pinned ? 0
                        : (spread > 0 ? ((int64_t)blockIdx.x * spread) % nb
                                      : dev::xcd_tile(blockIdx.x, nb)) << S_log2;
@@ -318,7 +320,7 @@ k_multi(SysMap map, Coef coef, const T *d, T *x, int64_t rhs_stride, int S_log2,
     }
 
     const int64_t off0 = sys.base + (int64_t)r0 * rs;
-    const int rows_out = pin && !pinned && sys.id == 0 ? 0 : rows_here;
+    const int rows_out = PIN && !pinned && sys.id == 0 ? 0 : rows_here;
 #pragma unroll
     for (int j = 0; j < M; ++j)
         if (j < rows_out) {
@@ -355,7 +357,7 @@ int64_t spread_stride(int64_t nb) {
     return k;
 }
 
-template <typename T, int M, int NR, bool SHIFT, bool VEC>
+template <typename T, int M, int NR, bool SHIFT, bool VEC, bool PIN = false>
 hipError_t launch_t(const SysMap &map, const Coef &coef, const MultiShape &sh, int64_t rhs_stride,
                     const void *d, void *x, const void *pin, int *err, hipStream_t st) {
     const int64_t S = (int64_t)1 << sh.S_log2;
@@ -365,7 +367,7 @@ hipError_t launch_t(const SysMap &map, const Coef &coef, const MultiShape &sh, i
     // full 128-byte tile rows: scattered tile order; narrower: XCD-aware
     const int64_t row_bytes = S * (int64_t)sizeof(T) * (VEC ? 2 : 1);
     const int64_t spread = row_bytes >= 128 ? spread_stride(blocks) : 0;
-    hipLaunchKernelGGL((k_multi<T, M, NR, SHIFT, VEC>), dim3((unsigned)(blocks + (pin ? 1 : 0))),
+    hipLaunchKernelGGL((k_multi<T, M, NR, SHIFT, VEC, PIN>), dim3((unsigned)(blocks + (PIN ? 1 : 0))),
                        dim3((unsigned)(S << sh.P_log2)), lds, st, map, coef, (const T *)d, (T *)x,
                        rhs_stride, sh.S_log2, sh.P_log2, spread, (const T *)pin, err);
     return hipGetLastError();
@@ -376,9 +378,16 @@ hipError_t launch_group(const SysMap &map, const Coef &coef, const MultiShape &s
                         bool vec, int64_t rhs_stride, const void *d, void *x, const void *pin,
                         int *err, hipStream_t st) {
     const bool shift = coef.shift != nullptr;
+    if (pin) {
+        // the FFT-Poisson step's own solve, the one caller that pins a system
+        if constexpr (sizeof(T) == 8)
+            if (nr == 2 && vec && shift)
+                return launch_t<T, M, 2, true, true, true>(map, coef, sh, rhs_stride, d, x, pin, err, st);
+        return hipErrorInvalidValue;
+    }
 #define TDMA_MULTI(NR, SH, V)                                                                   \
     if (nr == NR && shift == SH && vec == V)                                                    \
-        return launch_t<T, M, NR, SH, V>(map, coef, sh, rhs_stride, d, x, pin, err, st);
+        return launch_t<T, M, NR, SH, V>(map, coef, sh, rhs_stride, d, x, nullptr, err, st);
     TDMA_MULTI(2, true, true)
     TDMA_MULTI(2, false, true)
     TDMA_MULTI(2, true, false)
