@@ -528,9 +528,23 @@ __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n,
     // time so that their loads are in flight together: one complex line of 500
     // rows has 32 lanes and 14 such rows each, whose loads one row at a time
     // were 14 trips to memory in series (launch 22.6 us, at K = 4 9.1).  The
-    // one-tile-per-block kernels take K = 4; the walking ones keep 1 (the
-    // refinement walk on 14,756 lines of 882 rows: 639 us, at K = 4 711).
+    // multi-right-hand-side kernel takes K = 4, the generic one 2 (262,144 shifted
+    // x-lines of 16 rows, which have no such rows: 27.2 us at K = 1 and 2, 28.8 at 4;
+    // batches below 2^20 unknowns alike at 2 and 4, 4% slower at 1); the walking
+    // ones keep 1, with loads of rows inside the system alone (the refinement walk
+    // on 14,756 lines of 882 rows: 639 us, at K = 4 711; FP32 x-lines of 2000 rows,
+    // 2^25 unknowns, 157 us, with loads clamped to the last row 171).
     const T *A = (const T *)coef.a, *B = (const T *)coef.b, *C = (const T *)coef.c;
+    if constexpr (K == 1) {
+        for (int r = (int)threadIdx.x + CR * nth; r < R; r += nth) {
+            const bool in = r < n;
+            CO[r] = (LT)(in && r > 0 ? (double)A[r] : 0.0);
+            CO[R + r] = (LT)(in ? (double)B[r] : 1.0);
+            CO[2 * R + r] = (LT)(in && r < n - 1 ? (double)C[r] : 0.0);
+        }
+        __syncthreads();
+        return;
+    }
     for (int q = (int)threadIdx.x + CR * nth; q < R; q += K * nth) {
         double a[K], b[K], c[K];
 #pragma unroll
