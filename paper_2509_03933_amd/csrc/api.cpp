@@ -593,7 +593,9 @@ static void ragged_bucket(int64_t len, int *M_out, int *P_out) {
 // throughout 248 us, 256 and 512 227 us, 128, 256 and 512 242 us (each block
 // size is a launch of its own); beside the 768x512x1536 sweeps in a graph
 // the 256-lane blocks take CUs from the sweeps (graph 6.79 -> 6.86 ms), so
-// graphs build their plans with 512-lane blocks only.
+// graphs build their plans with 512-lane blocks (FP32 systems of more than
+// 8,192 rows 1024; 1024 for all of them slowed 50,000 FP32 systems of 500 to 1,000
+// rows from 323 to 350 us).
 int build_ragged_plan(const tdma_layout *L, int dtype, RaggedPlan *out, int min_block) {
     const int64_t nsys = L->nsys0;
     std::map<std::pair<int, int>, std::vector<int32_t>> buckets;   // (M, P) -> systems
@@ -634,7 +636,7 @@ int build_ragged_plan(const tdma_layout *L, int dtype, RaggedPlan *out, int min_
     std::vector<RaggedTile> tiles;
     auto block_of = [&](int M, int P) {
         const int maxt = fused_max_threads(dtype, M);
-        return std::min(maxt, std::max(min_block > 0 ? min_block : maxt, P));
+        return std::min(maxt, std::max(min_block, P));
     };
     std::vector<std::pair<int, int>> classes;   // (M, block lanes), largest blocks first
     for (const RaggedBucket &b : rp.buckets) {

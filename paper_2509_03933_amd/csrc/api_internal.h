@@ -74,8 +74,9 @@ Coef make_coef(const tdma_coeffs *C);
 bool default_shape(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shift,
                    TileShape *out);
 // min_block: the smallest block of the per-row tile list (lanes): 256 for a
-// batch solved on its own (two blocks share a CU), the kernel's largest block
-// (0 = that) for a batch that runs beside other work, as in a graph.
+// batch solved on its own (two blocks share a CU), 512 for a batch that runs
+// beside other work, as in a graph.
+constexpr int kRaggedBlockBeside = 512;
 int build_ragged_plan(const tdma_layout *L, int dtype, RaggedPlan *out, int min_block = 256);
 void free_ragged_plan(RaggedPlan *rp);
 int plan_ragged(DeviceCtx *ctx, const tdma_layout *L, int dtype, const RaggedPlan **out);
