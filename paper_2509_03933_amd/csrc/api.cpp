@@ -290,8 +290,9 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
 // blocks of 128 lanes below 2^19 unknowns, 256 (contiguous 512) above, and
 // most of a wavefront at least: short lines take up to 64 systems per block
 // (500,000 unknowns in z-lines of 2 rows, FP32 per-row: 118 us in blocks of one
-// lane, 7.5 in blocks of 64; walking 36).  The block has its lanes whatever the system count: those past the last system
-// load operator rows too.  Walking against generic kernel, us per call in a
+// lane, 7.5 in blocks of 64; walking 36).  The block has its lanes whatever the
+// system count: those past the last system load operator rows too.  Walking
+// against generic kernel, us per call in a
 // captured stream, FP64, lines of n rows x systems: shared z-lines 128 x 64
 // 9.7 / 5.1, 1000 x 64 23.1 / 8.7, 1000 x 1024 22.7 / 11.1, 1000 x 2500 28.5 /
 // 18.7, 1000 x 4096 26.1 / 26.6; shifted z-lines 250 x 256 8.5 / 5.7, 1000 x
@@ -797,7 +798,10 @@ int launch_ragged(const RaggedPlan &rp, const tdma_layout *L, const tdma_coeffs 
         return TDMA_OK;
     }
     const int nb = (int)rp.buckets.size();
-    const int nuse = std::max(0, std::min(naux, nb - 1));
+    // a stream for every two buckets: forking one more and joining it costs more
+    // than a small bucket's launch (2,000 shifted FP32 systems of 8 to 64 rows,
+    // three buckets: 63 us on two streams, 73 on three)
+    const int nuse = std::max(0, std::min(naux, nb / 2));
     hipError_t e = hipSuccess;
     if (nuse > 0) {
         e = hipEventRecord(ev[0], st);
