@@ -64,10 +64,12 @@ hipError_t launch_m(const SysMap &map, const Coef &coef, const TileShape &sh, co
     const bool shift = coef.shift != nullptr;
     const int dtype = sizeof(T) == 8 ? TDMA_F64 : TDMA_F32;
     const size_t lds_co = fused_lds_bytes(dtype, sh, true);
-    // (the two-level solve's spare slots, at most 11 KB where the limit is near,
-    // don't count: two blocks fit a CU with them too)
+    // the two-level solve's spare slots don't count: explicit tiles of 856 and more
+    // lanes pass 80 KB with them, one block per CU, and are the faster all the
+    // same (FP64 z-lines, 8 rows x 112 partitions x 8 systems: 48.9 us with one PCR
+    // and two blocks, 44.8)
     const int S = 1 << sh.S_log2;
-    const size_t spare = sh.contig ? 0 : dev::iface_lds_bytes(S, sh.P) - dev::pcr_lds_bytes(S, sh.P);
+    const size_t spare = sh.contig ? 0 : dev::iface_lds_bytes(S, sh.P, sh.pdd) - dev::pcr_lds_bytes(S, sh.P);
     const bool co = !like_d && lds_co - spare <= kCoLdsLimit;
     const size_t lds = co ? lds_co : fused_lds_bytes(dtype, sh, false);
 #define TDMA_DISPATCH(LD, SH, CT, C)                                                         \
@@ -129,8 +131,8 @@ size_t fused_lds_bytes(int dtype, const TileShape &sh, bool shared_rows) {
     const int S = 1 << sh.S_log2;
     const size_t esz = dtype == TDMA_F64 ? 8 : 4;
     if (shared_rows)
-        return fused_co_offset(esz, S, sh.P, sh.M, sh.contig) + 3 * (size_t)sh.P * sh.M * esz;
-    return fused_region0(esz, S, sh.P, sh.M, sh.contig, true) + (sh.contig ? (size_t)S * 16 : 0);
+        return fused_co_offset(esz, S, sh.P, sh.M, sh.contig, sh.pdd) + 3 * (size_t)sh.P * sh.M * esz;
+    return fused_region0(esz, S, sh.P, sh.M, sh.contig, sh.pdd, true) + (sh.contig ? (size_t)S * 16 : 0);
 }
 
 hipError_t launch_fused(int dtype, const SysMap &map, const Coef &coef, const TileShape &sh,

@@ -110,7 +110,7 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
         const int pitch = P * (M + 1) + 1;
         T *stg = reinterpret_cast<T *>(lds);
         const size_t stg_bytes = ((size_t)S * pitch * sizeof(T) + 15) & ~(size_t)15;
-        const size_t pcr_bytes = dev::iface_lds_bytes(S, P);
+        const size_t pcr_bytes = dev::iface_lds_bytes(S, P, PDD);
         TileSysLds *tsys = reinterpret_cast<TileSysLds *>(
             reinterpret_cast<char *>(lds) + (stg_bytes > pcr_bytes ? stg_bytes : pcr_bytes));
         if (tid < S) {
@@ -179,7 +179,7 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
         const int pitch = P * (M + 1) + 1;
         T *stg = reinterpret_cast<T *>(lds);
         const size_t stg_bytes = ((size_t)S * pitch * sizeof(T) + 15) & ~(size_t)15;
-        const size_t pcr_bytes = dev::iface_lds_bytes(S, P);
+        const size_t pcr_bytes = dev::iface_lds_bytes(S, P, PDD);
         TileSysLds *tsys = reinterpret_cast<TileSysLds *>(
             reinterpret_cast<char *>(lds) + (stg_bytes > pcr_bytes ? stg_bytes : pcr_bytes));
         dev::stage_out_sw<T, M>(stg, tsys, x, S, R, pitch, 1.0f / (float)R, s, p, dv);
@@ -194,17 +194,18 @@ __device__ __forceinline__ void fused_tile(const SysMap &map, const Coef &coef, 
 // generic tile stages with each lane's rows M+1 slots apart (sw, pitch
 // P*(M+1)+1), the shared-operator tile with pitch P*M+1.
 __host__ __device__ inline size_t fused_region0(size_t esz, int S, int P, int M, bool contig,
-                                                bool sw = false) {
-    const size_t pcr = dev::iface_lds_bytes(S, P);
+                                                bool pdd, bool sw = false) {
+    const size_t pcr = dev::iface_lds_bytes(S, P, pdd);
     if (!contig) return pcr;
     const size_t pitch = sw ? (size_t)P * (M + 1) + 1 : (size_t)P * M + 1;
     const size_t stg = ((size_t)S * pitch * esz + 15) & ~(size_t)15;
     return stg > pcr ? stg : pcr;
 }
 
-__host__ __device__ inline size_t fused_co_offset(size_t esz, int S, int P, int M, bool contig) {
+__host__ __device__ inline size_t fused_co_offset(size_t esz, int S, int P, int M, bool contig,
+                                                  bool pdd) {
     const size_t tsys = contig ? (size_t)S * 16 : 0;
-    return (fused_region0(esz, S, P, M, contig) + tsys + 15) & ~(size_t)15;
+    return (fused_region0(esz, S, P, M, contig, pdd) + tsys + 15) & ~(size_t)15;
 }
 
 // Fused tile of a shared operator (optionally with a per-system diagonal
@@ -225,7 +226,7 @@ __device__ __forceinline__ void fused_tile_co(const SysMap &map, const Coef &coe
     const LaneSys sys = dev::lane_system(map, k0 + s);
     const int rows_here = (int)(sys.nrows - r0 < 0 ? 0 : (sys.nrows - r0 > M ? M : sys.nrows - r0));
     char *base = reinterpret_cast<char *>(lds);
-    T *CO = reinterpret_cast<T *>(base + fused_co_offset(sizeof(T), S, P, M, CONTIG));
+    T *CO = reinterpret_cast<T *>(base + fused_co_offset(sizeof(T), S, P, M, CONTIG, PDD));
 
     // coefficient rows first, then the right-hand sides (in flight while the
     // rows go to LDS)
@@ -235,7 +236,7 @@ __device__ __forceinline__ void fused_tile_co(const SysMap &map, const Coef &coe
     __builtin_amdgcn_sched_barrier(0);
     T dv[M];
     T *stg = reinterpret_cast<T *>(lds);
-    TileSysLds *tsys = reinterpret_cast<TileSysLds *>(base + fused_region0(sizeof(T), S, P, M, CONTIG));
+    TileSysLds *tsys = reinterpret_cast<TileSysLds *>(base + fused_region0(sizeof(T), S, P, M, CONTIG, PDD));
     const float invR = 1.0f / (float)R;
     if constexpr (!CONTIG) {
         // branch-free, so the loads form one run behind the coefficient rows:

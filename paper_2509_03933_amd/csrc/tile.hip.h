@@ -118,9 +118,10 @@ __host__ __device__ constexpr size_t pcr_lds_bytes(int S, int P) {
     return (size_t)3 * S * (2 * P + 1) * sizeof(double);
 }
 
-// The same for the kernels that solve above 64 partitions in two levels.
-__host__ __device__ constexpr size_t iface_lds_bytes(int S, int P) {
-    return P > 64 ? (size_t)3 * S * two_level_pitch(P) * sizeof(double) : pcr_lds_bytes(S, P);
+// The same for the kernels that solve above 64 partitions in two levels (the
+// PDD approximation has no such solve).
+__host__ __device__ constexpr size_t iface_lds_bytes(int S, int P, bool pdd) {
+    return P > 64 && !pdd ? (size_t)3 * S * two_level_pitch(P) * sizeof(double) : pcr_lds_bytes(S, P);
 }
 
 // Interface rows of one partition (unit diagonal): first row couples
