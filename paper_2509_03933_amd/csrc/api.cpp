@@ -56,6 +56,8 @@ void DeviceCtx::release() {
     workspaces.clear();
     for (auto e : events) (void)hipEventDestroy(e);
     events.clear();
+    if (staged_done) (void)hipEventDestroy(staged_done);
+    staged_done = nullptr;
     for (auto s : streams) (void)hipStreamDestroy(s);
     streams.clear();
     if (d_err) (void)hipFree(d_err);

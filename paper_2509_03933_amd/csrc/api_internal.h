@@ -56,6 +56,9 @@ struct DeviceCtx {
     std::vector<hipStream_t> streams;
     std::vector<hipEvent_t> events;
     std::vector<Workspace> workspaces;
+    // recorded behind the last staged solve (null before the first): the next
+    // one, whatever its stream, waits for it before it uses their workspace
+    hipEvent_t staged_done = nullptr;
     std::map<uint64_t, RaggedPlan> ragged_cache;
     ~DeviceCtx();
     void release();

@@ -20,59 +20,23 @@
 
 namespace tdma {
 
-int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int dtype,
-                   const void *d, void *x, int P, int64_t batch, int nstreams, int schedule,
-                   hipStream_t caller) {
-    const SysMap map = make_map(L);
-    const Coef coef = make_coef(C);
+// The batches of a staged solve in their slots: on the caller's stream if there
+// is one alone (nothing to overlap with), else on nstreams library streams
+// forked from it and joined back.
+static int run_batches(DeviceCtx *ctx, const SysMap &map, const Coef &coef, int dtype, const void *d, void *x,
+                       int P, int64_t batch, int64_t nbatches, const std::vector<StageWs> &slots, int nstreams,
+                       int schedule, hipStream_t caller) {
     const int64_t nsys = map.nsys;
-    if (nsys == 0) return TDMA_OK;
-    batch = std::max<int64_t>(1, std::min(batch, nsys));
-    const int64_t nbatches = (nsys + batch - 1) / batch;
-    int nslots = schedule == 0 ? 3 : nstreams;
-    nslots = (int)std::max<int64_t>(1, std::min<int64_t>(nslots, nbatches));
-
-    // per-slot workspace
-    std::vector<StageWs> slots(nslots);
-    const size_t slot_bytes = stage_ws(dtype, map, coef, batch, P, nullptr, &slots[0]);
-    void *ws = nullptr;
-    int rc = ctx->workspace(1, slot_bytes * nslots, &ws);
-    if (rc != TDMA_OK) return rc;
-    for (int i = 0; i < nslots; ++i)
-        (void)stage_ws(dtype, map, coef, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
-
-    // One batch has nothing to overlap with: its three stages run in sequence on
-    // the library's first stream, with one fork and join.  Not on the caller's
-    // own stream: the workspace is one per device, and the one-batch calls of
-    // several streams follow one another on that stream.  (A caller that records
-    // a graph has them on its own stream, in the graph.)
+    const int nslots = (int)slots.size();
     if (nbatches == 1) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        hipError_t e = hipStreamIsCapturing(caller, &cs);
-        if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
-        const bool own = cs == hipStreamCaptureStatusNone;
-        hipStream_t q = caller, *lib = nullptr;
-        hipEvent_t *ev = nullptr;
-        if (own) {
-            rc = ctx->get_streams(1, &lib);
-            if (rc == TDMA_OK) rc = ctx->get_events(2, &ev);
-            if (rc != TDMA_OK) return rc;
-            q = lib[0];
-            e = hipEventRecord(ev[0], caller);
-            if (e == hipSuccess) e = hipStreamWaitEvent(q, ev[0], 0);
-        }
-        if (e == hipSuccess) e = launch_stage_a(dtype, map, coef, d, slots[0], 0, nsys, P, ctx->d_err, q);
-        if (e == hipSuccess) e = launch_stage_b(slots[0], nsys, P, ctx->d_err, q);
-        if (e == hipSuccess) e = launch_stage_c(dtype, map, coef, d, x, slots[0], 0, nsys, P, q);
-        if (own && e == hipSuccess) {
-            e = hipEventRecord(ev[1], q);
-            if (e == hipSuccess) e = hipStreamWaitEvent(caller, ev[1], 0);
-        }
+        hipError_t e = launch_stage_a(dtype, map, coef, d, slots[0], 0, nsys, P, ctx->d_err, caller);
+        if (e == hipSuccess) e = launch_stage_b(slots[0], nsys, P, ctx->d_err, caller);
+        if (e == hipSuccess) e = launch_stage_c(dtype, map, coef, d, x, slots[0], 0, nsys, P, caller);
         return e == hipSuccess ? TDMA_OK : hip_fail(e, "pipeline launch");
     }
 
     hipStream_t *streams = nullptr;
-    rc = ctx->get_streams(nstreams, &streams);
+    int rc = ctx->get_streams(nstreams, &streams);
     if (rc != TDMA_OK) return rc;
     hipEvent_t *ev = nullptr;
     // events: [0] fork, [1 .. nstreams] joins, then evA/evB/evC per slot
@@ -143,6 +107,50 @@ int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, i
     }
     if (e != hipSuccess) return hip_fail(e, "pipeline join");
     return TDMA_OK;
+}
+
+int pipeline_solve(DeviceCtx *ctx, const tdma_layout *L, const tdma_coeffs *C, int dtype,
+                   const void *d, void *x, int P, int64_t batch, int nstreams, int schedule,
+                   hipStream_t caller) {
+    const SysMap map = make_map(L);
+    const Coef coef = make_coef(C);
+    const int64_t nsys = map.nsys;
+    if (nsys == 0) return TDMA_OK;
+    batch = std::max<int64_t>(1, std::min(batch, nsys));
+    const int64_t nbatches = (nsys + batch - 1) / batch;
+    int nslots = schedule == 0 ? 3 : nstreams;
+    nslots = (int)std::max<int64_t>(1, std::min<int64_t>(nslots, nbatches));
+
+    // per-slot workspace
+    std::vector<StageWs> slots(nslots);
+    const size_t slot_bytes = stage_ws(dtype, map, coef, batch, P, nullptr, &slots[0]);
+    void *ws = nullptr;
+    int rc = ctx->workspace(1, slot_bytes * nslots, &ws);
+    if (rc != TDMA_OK) return rc;
+    for (int i = 0; i < nslots; ++i)
+        (void)stage_ws(dtype, map, coef, batch, P, (char *)ws + slot_bytes * i, &slots[i]);
+
+    // The workspace is one per device: the caller's stream waits for the staged
+    // solve before this one, whatever stream that came from, and leaves an event
+    // behind its own work.  A stream that is being recorded into a graph can do
+    // neither; the order of such a graph's launches is the caller's.
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(caller, &cs);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+    const bool ordered = cs == hipStreamCaptureStatusNone;
+    if (ordered && ctx->staged_done) {
+        e = hipStreamWaitEvent(caller, ctx->staged_done, 0);
+        if (e != hipSuccess) return hip_fail(e, "wait for the last staged solve");
+    } else if (ordered) {
+        e = hipEventCreateWithFlags(&ctx->staged_done, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail(e, "hipEventCreate");
+    }
+    rc = run_batches(ctx, map, coef, dtype, d, x, P, batch, nbatches, slots, nstreams, schedule, caller);
+    if (ordered) {
+        e = hipEventRecord(ctx->staged_done, caller);
+        if (e != hipSuccess && rc == TDMA_OK) return hip_fail(e, "staged solve's event");
+    }
+    return rc;
 }
 
 }  // namespace tdma
