@@ -24,9 +24,11 @@ def _runs(n, run, planes):
 
 LAYOUTS = {
     "contiguous": lambda n: Layout(n=n, nsys0=300, row_stride=1, sys_stride0=n),
-    "stride2": lambda n: Layout(n=n, nsys0=150, row_stride=300, sys_stride0=2),
+    "contiguous_many": lambda n: Layout(n=n, nsys0=2050, row_stride=1, sys_stride0=n),
+    "stride2": lambda n: Layout(n=n, nsys0=1030, nsys1=2, row_stride=2060, sys_stride0=2, sys_stride1=2060 * n),
     "run1": lambda n: Layout(n=n, nsys0=1, nsys1=300, row_stride=300, sys_stride0=7, sys_stride1=1),
     "run2": lambda n: _runs(n, 2, 150),
+    "run2_many": lambda n: _runs(n, 2, 1030),
     "run7": lambda n: _runs(n, 7, 43),
     "run8": lambda n: _runs(n, 8, 38),
     "run15": lambda n: _runs(n, 15, 20),
