@@ -228,7 +228,8 @@ static int contig_perrow_s_log2(int64_t P) {
 // registers of 16 and twice the blocks run per CU, one's loads beside the
 // other's arithmetic: 120,000 x 720 rows 785 -> 695 us (M = 16, S = 4 against
 // M = 8, S = 2), 120,000 x 250 255 -> 228, 16,384 x 1000 161 -> 135, 40,000 x
-// 1500 552 -> 511; 5,504 x 3000 168 at 16 rows, 209 at 8.  In FP32, 16 rows
+// 1500 552 -> 511.  Around the line, 2^24 unknowns, 8 rows against 16: 2000 rows
+// 136 and 147, 2300 208 and 198, 3000 188 and 166.  In FP32, 16 rows
 // take those registers already and 8 measured slower (436 against 515 us).
 // Systems per block: contig_perrow_s_log2 (41,856 x 400: S = 1, 50 lanes, 136
 // us, S = 2 149; 27,904 x 600: S = 2, 150 lanes, 157, S = 1 176).

@@ -3,10 +3,11 @@
 // per-row z-lines of a 3-D grid, rows 2^20 elements apart at 1024^3).
 //
 // Resident workgroups walk tiles of S systems x P partitions x M rows per
-// lane.  S is 16 FP64 (32 FP32) systems, so every row of a tile is one
-// 128-byte line and each address translation serves 128 bytes; this is what
-// the one-tile-per-block kernel (S = 8, 64-byte rows) cannot reach, because
-// it holds all four inputs of every row.  Here a lane keeps three values per
+// lane.  S is as many systems as the lanes allow (16 to 128, so every row of a
+// tile is a 128-byte line or more and each address translation serves that much;
+// fewer with 64 partitions or few tiles); this is what the one-tile-per-block
+// kernel (S = 8, 64-byte rows) cannot reach, because it holds all four inputs of
+// every row.  Here a lane keeps three values per
 // interior row, alpha_j = g_j a_j, gamma_j = g_j c_j and delta_j = g_j d_j
 // (g_j the pivot reciprocal of plain Thomas on the rows 1..M-2 with x_0 as a
 // boundary value), computed as the rows arrive:

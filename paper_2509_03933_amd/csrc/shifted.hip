@@ -589,12 +589,14 @@ k_shift_stream(SysMap map, Coef coef, const T *d, T *x, int S_log2, int P_log2, 
 // for.  The rows of d are not held: a residual reads them again (from the
 // caches, the tile's are 128 KB) through a window of 16 loads in flight, and
 // the registers of x, free from a tile's end to its first correction, take
-// the next tile's rows of d as the rows of x are stored.  Nothing spills (67
-// registers did with d held) and Stage B fits in its DPP form.  512^3 Poisson
+// the next tile's rows of d as the rows of x are stored.  Where 32 rows x P
+// cover n nothing spills (67 registers did with d held; 37 to 39 do on other
+// lengths, whose rows past the end are tested one by one) and Stage B fits in its
+// DPP form.  512^3 Poisson
 // lines, two steps: 1416 us with d held; 1337 read again at the residual;
 // 1244 with the DPP Stage B; 1008 with the window and the rolled loads (16 B
-// per unknown: 2.1 TB/s).  16 rows per lane (four waves per SIMD, 30
-// registers spilled, twice the interface rows): 1746.
+// per unknown: 2.1 TB/s).  16 rows per lane (four waves per SIMD, with
+// spills, twice the interface rows): 1746.
 
 // Second LDS part of the refinement, after the FP64 layout: FP32 copies of
 // the operator rows (a, b, c, m per row, pitch M+1 per partition), then the
