@@ -175,8 +175,9 @@ __device__ __forceinline__ void shared_tables(const Coef &coef, int64_t n, const
     double *QC = QA + L.nsteps * 2 * P, *QB = QC + L.nsteps * 2 * P;
     // coefficient tables, one lane per partition (FP64 arithmetic), from a
     //    copy of the tile's coefficient rows in LDS (corners and padding removed)
-    dev::rows_commit<CT, shared_cr<M>()>(reinterpret_cast<double *>(base + L.co), coef, n, P * M,
-                                         cr);
+    // (the refinement's FP32 tables of an FP64 operator load clamped rows)
+    dev::rows_commit<CT, shared_cr<M>(), double, 1, std::is_same<T, CT>::value>(
+        reinterpret_cast<double *>(base + L.co), coef, n, P * M, cr);
     if (s == 0) {
         const double *CO = reinterpret_cast<const double *>(base + L.co);
         const int R = P * M;

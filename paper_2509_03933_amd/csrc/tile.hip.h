@@ -511,7 +511,7 @@ __device__ __forceinline__ void rows_prefetch(const Coef &coef, int64_t n, RowRe
     }
 }
 
-template <typename T, int CR, typename LT = double, int K = 1>
+template <typename T, int CR, typename LT = double, int K = 1, bool SKIP = false>
 __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n, int R,
                                             const RowRegs<CR> &rr) {
     const int nth = (int)blockDim.x;
@@ -532,11 +532,14 @@ __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n,
     // multi-right-hand-side kernel takes K = 4, the generic one 2 (262,144 shifted
     // x-lines of 16 rows, which have no such rows: 27.2 us at K = 1 and 2, 28.8 at 4;
     // batches below 2^20 unknowns alike at 2 and 4, 4% slower at 1); the walking
-    // ones keep 1, with loads of rows inside the system alone (the refinement walk
-    // on 14,756 lines of 882 rows: 639 us, at K = 4 711; FP32 x-lines of 2000 rows,
-    // 2^25 unknowns, 157 us, with loads clamped to the last row 171).
+    // ones keep 1 (the refinement walk on 14,756 lines of 882 rows: 639 us, at K =
+    // 4 711).  SKIP: rows past the system's end are skipped instead of loaded from
+    // its last row, which the streaming kernels want (FP32 x-lines of 2000 rows,
+    // 2^25 unknowns, 157 us, clamped 171) and the refinement kernels do not (one
+    // line of 1024 rows: 46 us, clamped 37: a later row's loads need not wait for
+    // an earlier row's test).
     const T *A = (const T *)coef.a, *B = (const T *)coef.b, *C = (const T *)coef.c;
-    if constexpr (K == 1) {
+    if constexpr (K == 1 && SKIP) {
         for (int r = (int)threadIdx.x + CR * nth; r < R; r += nth) {
             const bool in = r < n;
             CO[r] = (LT)(in && r > 0 ? (double)A[r] : 0.0);
