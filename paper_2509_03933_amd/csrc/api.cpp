@@ -322,9 +322,10 @@ bool default_shared_shape(int dtype, int64_t n, int64_t nsys, bool contig, TileS
 // 38.6; 2^20.9: 27.1 / 24.7), shifted FP64 ones 2^20 (2000 rows in y, 2^21.2: 21.6 /
 // 39.5) and 2^21 where they fill 64 partitions (2048 rows, 2^20.8: 35.3 / 25.8), per-row
 // lines of 512 rows, which fill 16 partitions, 2^20 (in y, 2^20.2: 15.2 / 24.4).
-// FP32 shared ones against their small tiles: 2^20 up to 256 rows, 3 x 2^19 where the
-// streaming kernel has 12 or 24 rows per lane (640 rows, 2^21.4: 17 / 27; 512 rows
-// 13.6 / 11.4).  Past 2,048 rows 2^20 for per-row lines and shifted FP32 ones (4096
+// FP32 shared ones against their small tiles: 2^20 from 129 to 256 rows (250 rows in
+// y, 2^20.3: 1.10 of the walking time), 3 x 2^19 up to 128 rows (2^20.3: 0.86) and
+// where the streaming kernel has 12 or 24 rows per lane (640 rows, 2^21.4: 17 / 27;
+// 512 rows 13.6 / 11.4).  Past 2,048 rows 2^20 for per-row lines and shifted FP32 ones (4096
 // rows, 2^19.3: 29 / 24; 2500 rows, 2^20.3: 27 / 46), none for the others (614 FP64
 // lines of 4096 rows: 37 / 50).
 static int64_t small_limit(int dtype, int64_t n, int64_t nsys, bool contig, bool like_d, bool shared_op) {
@@ -333,9 +334,11 @@ static int64_t small_limit(int dtype, int64_t n, int64_t nsys, bool contig, bool
     if (n > 2048) return like_d || (dtype == TDMA_F32 && !shared_op) ? 2 * k19 : 0;
     if (like_d) return n == 16 * 32 ? 2 * k19 : 3 * k19;
     if (shared_op) {
-        if (n <= 48 || (dtype == TDMA_F32 && n <= 256)) return 2 * k19;
+        if (n <= 48 || (dtype == TDMA_F32 && n > 128 && n <= 256)) return 2 * k19;
         TileShape w;
-        if (dtype == TDMA_F32 && default_shared_shape(dtype, n, nsys, false, &w, true) && (w.M == 12 || w.M == 24))
+        if (dtype == TDMA_F32 &&
+            (n <= 128 ||
+             (default_shared_shape(dtype, n, nsys, false, &w, true) && (w.M == 12 || w.M == 24))))
             return 3 * k19;
     }
     if (n > 1024 && dtype == TDMA_F64) return shared_op || n == 64 * 32 ? 4 * k19 : 2 * k19;

@@ -266,7 +266,7 @@ __device__ __forceinline__ void fused_tile_co(const SysMap &map, const Coef &coe
         sh = ((const T *)coef.shift)[sys.valid ? sys.id : 0];
         if (!sys.valid) sh = T(0);
     }
-    dev::rows_commit<T, CR, T, 2>(CO, coef, map.n, R, rr);
+    dev::rows_commit<T, CR, T, CONTIG ? 2 : 4>(CO, coef, map.n, R, rr);
     if constexpr (!CONTIG) {
 #pragma unroll
         for (int j = 0; j < M; ++j)

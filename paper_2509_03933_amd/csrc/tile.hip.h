@@ -529,9 +529,11 @@ __device__ __forceinline__ void rows_commit(LT *CO, const Coef &coef, int64_t n,
     // time so that their loads are in flight together: one complex line of 500
     // rows has 32 lanes and 14 such rows each, whose loads one row at a time
     // were 14 trips to memory in series (launch 22.6 us, at K = 4 9.1).  The
-    // multi-right-hand-side kernel takes K = 4, the generic one 2 (262,144 shifted
-    // x-lines of 16 rows, which have no such rows: 27.2 us at K = 1 and 2, 28.8 at 4;
-    // batches below 2^20 unknowns alike at 2 and 4, 4% slower at 1); the walking
+    // multi-right-hand-side kernel and the generic one on strided rows take K = 4
+    // (one FP64 line of 1024 rows 20 us, 24 at K = 2), the generic one on
+    // contiguous rows 2 (262,144 shifted lines of 16 rows, which have no such rows:
+    // 27.2 us at K = 1 and 2, 28.8 at 4; batches below 2^20 unknowns alike at 2 and
+    // 4, 4% slower at 1); the walking
     // ones keep 1 (the refinement walk on 14,756 lines of 882 rows: 639 us, at K =
     // 4 711).  SKIP: rows past the system's end are skipped instead of loaded from
     // its last row, which the streaming kernels want (FP32 x-lines of 2000 rows,
