@@ -501,15 +501,18 @@ hipError_t launch_c_t(const SysMap &map, const Coef &coef, const void *d, void *
 // runs of 4: 0.23 and 0.30, of 8: 0.16 and 0.15 per-row at 250 rows), and where
 // partitions have fewer than kSeg / 2 interior rows, whose segment reads and
 // eliminates kSeg rows all the same (400,000 lines of 40 rows, 5 per partition:
-// 0.27 ms keeping rows, 0.33 keeping states).  Fewer systems than 256 (2,048 of a
-// shared operator) wait for their loads, not for memory's rate, and a segment's
-// loads are in flight together: they keep states (64 contiguous per-row lines of
-// 5000 rows 1.30 times as long keeping rows, 256 0.89; shared and shifted ones, FP64:
-// 64 1.29, 1,024 1.05 and 1.11, 3,000 0.58 and 0.75).
-static bool stage_keeps_rows(const SysMap &map, size_t esz, int P, bool per_row) {
+// 0.27 ms keeping rows, 0.33 keeping states).  Few systems wait for their loads,
+// not for memory's rate, and a segment's loads are in flight together: they keep
+// states.  The line lies where the two meet, on contiguous lines of 5000 to
+// 40,000 rows (time keeping rows over time keeping states): shared operator 512
+// systems 0.92 to 1.31, 1000 0.73 to 1.06, 2000 0.51 to 0.68; with a shift 1000
+// 0.85 to 1.32, 1500 0.75 to 1.07, 2000 0.72 to 0.92; per-row FP32 64 0.79 to
+// 0.87, FP64 64 1.25 to 1.33, 128 0.87 to 1.19.
+static bool stage_keeps_rows(const SysMap &map, size_t esz, int P, const Coef &coef) {
     const int64_t stride = map.nsys0 > 1 ? map.sys_stride0 : map.sys_stride1;
     const int64_t run = map.nsys0 > 1 ? map.nsys0 : map.nsys;
-    if (map.nsys < (per_row ? 256 : 2048)) return false;
+    const int64_t few = coef.mode == TDMA_COEF_LIKE_D ? (esz == 4 ? 64 : 160) : coef.shift ? 1280 : 768;
+    if (map.nsys < few) return false;
     return stride != 1 || run * (int64_t)esz < 64 || map.n / P - 2 < kSeg / 2;
 }
 
@@ -521,7 +524,7 @@ size_t stage_ws(int dtype, const SysMap &map, const Coef &coef, int64_t batch, i
     const int64_t mmax = n / P + (n % P != 0);
     const int64_t nseg = mmax > 2 ? (mmax - 2 + kSeg - 1) / kSeg : 0;
     const bool shared_factors = coef.mode == TDMA_COEF_SHARED && coef.shift == nullptr;
-    out->keep_rows = stage_keeps_rows(map, esz, P, coef.mode == TDMA_COEF_LIKE_D);
+    out->keep_rows = stage_keeps_rows(map, esz, P, coef);
     const size_t states = out->keep_rows ? (size_t)n : (size_t)P * nseg;
     const size_t d_bytes = al(states * batch * esz);
     const size_t f_bytes = shared_factors ? al(states * esz) : d_bytes;
